@@ -110,6 +110,20 @@ __device__ __forceinline__ int choose_log2_slices(int n, int per_round) {
     return best;
 }
 
+// Slices that spread a group of n members over the 8 virtual wavefronts of one
+// round (n <= 512), for a group of which many blocks hold a part each: its
+// lanes then have few entries of a part one after the other.
+__device__ __forceinline__ int fill_log2_slices(int n) {
+    int ls = 6;
+    while (ls > 0 && n > (8 * kWave >> ls)) --ls;
+    return ls;
+}
+
+// The 256-entry tiles of a group's lists that make one unit of its interaction
+// kernel: FP32 folds its partial sums into the compensated ones after at least
+// 64 entries per lane, so a unit is the tiles between two folds.
+__device__ __forceinline__ int fold_tiles(int ls) { return ls > 2 ? 1 << (ls - 2) : 1; }
+
 // Common leading octal digits (tree levels) of two 63-bit Morton keys: 21 if equal.
 __device__ __forceinline__ int common_levels(uint64_t a, uint64_t b) {
     uint64_t d = a ^ b;

@@ -29,6 +29,9 @@
 //    middle branch is evaluated in FP64 in both paths (its monomial form
 //    cancels by two orders of magnitude).  Accepted cells lie at least h from
 //    the group, so their K = W = 1 is tested only when h < r_out;
+//  * a launch of one block per group ends with its largest group, so where
+//    groups are few they are split into parts of their lists (walk.hip decides
+//    which), a block each, whose sums k_force_fold adds up;
 //  * the mixed path accumulates each tile in FP32 and adds tile partials to a
 //    compensated (Kahan) FP32 sum per particle and component.
 #include <math.h>
@@ -120,6 +123,12 @@ struct alignas(16) CJ {
     R x, y, z, M, qxx, qyy, qzz, qxy, qxz, qyz;
 };
 
+// a partial sum of a split group (see k_force_fold)
+template <class R>
+struct alignas(4 * sizeof(R)) Part {
+    R ax, ay, az, ph;
+};
+
 // i-particle slot: position offset, tile partials and compensated sums
 template <class R>
 struct Slot {
@@ -132,6 +141,11 @@ struct Slot {
     __device__ __forceinline__ void flush() {
         if (sizeof(R) == 8) return;
         sx.add(ax); sy.add(ay); sz.add(az); sp.add(ph);
+        ax = ay = az = ph = R(0);
+    }
+    // FP32, split group: the partials go to memory instead
+    __device__ __forceinline__ void park(Part<R> *p) {
+        *p = Part<R>{ax, ay, az, ph};
         ax = ay = az = ph = R(0);
     }
     __device__ __forceinline__ double total(int c) const {
@@ -245,9 +259,9 @@ __device__ __forceinline__ void pc_term(Slot<R> &q, const CJ<R> &c, R eps2, R ro
 // slice), so unrolled iterations read at immediate offsets from one address.
 // Trip counts are wave-uniform: lanes past the end of a tile read the padding
 // entries (zero mass, far away), whose terms are exactly zero.
-template <class R, bool TWO>
+template <class R, bool TWO, int UNROLL>
 __device__ __forceinline__ void far_tile(Slot<R> *q, const PJ<R> *sp, int iters, R eps2) {
-#pragma unroll(sizeof(R) == 8 ? 4 : 2)
+#pragma unroll UNROLL
     for (int it = 0; it < iters; ++it, ++sp) {
         const PJ<R> pj = *sp;
         pp_fast<R>(q[0], pj, eps2);
@@ -282,10 +296,10 @@ __device__ __forceinline__ void near_tile(Slot<R> *q, const PJ<R> *sp, const int
     }
 }
 
-template <class R, bool QUAD, bool CHECK_K, bool TWO>
+template <class R, bool QUAD, bool CHECK_K, bool TWO, int UNROLL>
 __device__ __forceinline__ void cell_tile(Slot<R> *q, const CJ<R> *sc, int iters, R eps2, R rout2,
                                           const ForceParams &fp) {
-#pragma unroll(sizeof(R) == 8 ? 4 : 2)
+#pragma unroll UNROLL
     for (int it = 0; it < iters; ++it, ++sc) {
         const CJ<R> cj = *sc;
         pc_term<R, QUAD, CHECK_K>(q[0], cj, eps2, rout2, fp);
@@ -297,12 +311,24 @@ __device__ __forceinline__ void cell_tile(Slot<R> *q, const CJ<R> *sc, int iters
 // their registers, a few values of the near path and of the tile loop go to
 // scratch), which hides more latency than four of 118 VGPRs; FP64, four (128
 // VGPRs).
-template <class R, bool QUAD, bool CHECK_K>
+// SPLIT: blocks may hold part of a split group (with the compensated sums of a
+// whole group beside it, the FP32 kernel spills in its loops, so whole groups
+// have a kernel without).
+template <class R, bool QUAD, bool CHECK_K, bool SPLIT>
 __global__ __launch_bounds__(kForceThreads)
-__attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 4 : 5))) void k_force(
-    const GroupInfo *__restrict__ grp, ListsDev L, const PosMass *__restrict__ xm,
+__attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 || SPLIT ? 4 : 5))) void k_force(
+    const GroupInfo *__restrict__ grp, ListsDev L, WorkDev wd, const SplitGroup *__restrict__ sg,
+    Part<R> *__restrict__ part, const PosMass *__restrict__ xm,
     const NodeMP *__restrict__ mp, const int32_t *__restrict__ perm, ForceParams fp,
     double *__restrict__ acc, double *__restrict__ pot) {
+    // the FP32 kernel of the split groups runs where wavefronts are few
+    constexpr int kUnroll = sizeof(R) == 8 || SPLIT ? 4 : 2;
+    int64_t item = blockIdx.x;
+    if (SPLIT) {
+        if (item < wd.first_whole && item >= *wd.n_split_items) return;
+    } else {
+        item += wd.first_whole;
+    }
     // one tile, stored slice by slice (see below)
     __shared__ PJ<R> s_p[kTile + kWave];
     __shared__ int32_t s_jid[kTile + kWave];
@@ -313,18 +339,21 @@ __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 4 : 5))) void k_force(
     zero_c.M = zero_c.qxx = zero_c.qyy = zero_c.qzz = zero_c.qxy = zero_c.qxz = zero_c.qyz = R(0);
 
     const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
-    const int g = L.order[blockIdx.x];
+    const WorkItem wi = wd.items[item];
+    const int g = wi.g;
     const GroupInfo gi = grp[g];
     const double gcx = gi.c[0], gcy = gi.c[1], gcz = gi.c[2];
-    const int64_t cb = L.beg[0][g], ce = L.end[0][g];
-    const int64_t pb = L.beg[1][g], pe = L.end[1][g];
-    const int64_t nb = L.beg[2][g], ne = L.end[2][g];
+    int64_t cb = L.beg[0][g], ce = L.end[0][g];
+    int64_t pb = L.beg[1][g], pe = L.end[1][g];
+    int64_t nb = L.beg[2][g], ne = L.end[2][g];
     const int32_t *__restrict__ c_idx = L.idx[0];
     const int32_t *__restrict__ p_idx = L.idx[1];
     const int32_t *__restrict__ n_idx = L.idx[2];
     const R eps2 = (R)fp.eps2, rout2 = (R)fp.rout2;
 
-    const int ls = choose_log2_slices(gi.count, 2 * kForceWaves);
+    const bool one_round = SPLIT && wi.round >= 0;
+    const int ls = sizeof(R) == 8 && one_round ? fill_log2_slices(gi.count)
+                                               : choose_log2_slices(gi.count, 2 * kForceWaves);
     const int ns = 1 << ls;
     const int nw = kWave >> ls;                 // i-particles per virtual wavefront
     const int il = lane & (nw - 1), slice = lane >> (6 - ls);
@@ -338,8 +367,24 @@ __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 4 : 5))) void k_force(
     const int S = (kTile >> ls) + 1;
     const int spos = (tid & (ns - 1)) * S + (tid >> ls);   // this thread's staging slot
     const int sbase = slice * S;                            // this lane's slice
+    // this block's part of a split group's lists
+    Part<R> *fold_to = nullptr;     // FP32: the next fold's partial sums, [unit][V][64]
+    if (SPLIT && wi.parts > 1) {
+        const int64_t ul = (int64_t)kTile * (sizeof(R) == 8 ? 1 : fold_tiles(ls));
+        const int64_t units[3] = {(ce - cb + ul - 1) / ul, (pe - pb + ul - 1) / ul,
+                                  (ne - nb + ul - 1) / ul};
+        const PartRange r = part_range(units, wi.part, wi.parts);
+        fold_to = part + sg[g].base;
+        if (sizeof(R) == 4)   // far units first, then near, then cells
+            fold_to += (r.lo[0] + r.lo[1] + r.lo[2]) * V * kWave;
+        ce = min(ce, cb + r.hi[0] * ul); cb += r.lo[0] * ul;
+        pe = min(pe, pb + r.hi[1] * ul); pb += r.lo[1] * ul;
+        ne = min(ne, nb + r.hi[2] * ul); nb += r.lo[2] * ul;
+    }
 
-    for (int v0 = 0; v0 < V; v0 += 2 * kForceWaves) {
+    const int v_from = one_round ? wi.round * 2 * kForceWaves : 0;
+    const int v_to = one_round ? min(V, v_from + 2 * kForceWaves) : V;
+    for (int v0 = v_from; v0 < v_to; v0 += 2 * kForceWaves) {
         // this wavefront's two virtual wavefronts (i-slots) in this round
         const bool act0 = v0 + w < V, act1 = v0 + kForceWaves + w < V;
         Slot<R> q[2];
@@ -358,11 +403,18 @@ __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 4 : 5))) void k_force(
         }
         // FP32 partials are folded into the compensated sums every >= 64 iterations
         int since = 0;
+        Part<R> *fold_now = fold_to;
         auto fold = [&](int iters, bool last) {
             since += iters;
             if (since >= 64 || last) {
-                if (act0) q[0].flush();
-                if (act1) q[1].flush();
+                if (SPLIT && sizeof(R) == 4 && fold_to) {   // a split group: k_force_fold adds them
+                    if (act0) q[0].park(fold_now + (v0 + w) * kWave + lane);
+                    if (act1) q[1].park(fold_now + (v0 + kForceWaves + w) * kWave + lane);
+                    fold_now += V * kWave;
+                } else {
+                    if (act0) q[0].flush();
+                    if (act1) q[1].flush();
+                }
                 since = 0;
             }
         };
@@ -401,8 +453,8 @@ __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 4 : 5))) void k_force(
         };
         // far particles: K = W = 1 and j != i, plain softened terms
         stream_particles(p_idx, pb, pe, [&](int iters) {
-            if (act1) far_tile<R, true>(q, s_p + sbase, iters, eps2);
-            else if (act0) far_tile<R, false>(q, s_p + sbase, iters, eps2);
+            if (act1) far_tile<R, true, kUnroll>(q, s_p + sbase, iters, eps2);
+            else if (act0) far_tile<R, false, kUnroll>(q, s_p + sbase, iters, eps2);
         });
         // near particles: changeover and self exclusion where s < r_out
         stream_particles(n_idx, nb, ne, [&](int iters) {
@@ -430,9 +482,9 @@ __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 4 : 5))) void k_force(
                 pre = (t0 + kTile + tid < ce) ? load_cell(t0 + kTile + tid) : zero_c;
                 const int iters = (tl + ns - 1) >> ls;
                 if (act1)
-                    cell_tile<R, QUAD, CHECK_K, true>(q, s_c + sbase, iters, eps2, rout2, fp);
+                    cell_tile<R, QUAD, CHECK_K, true, kUnroll>(q, s_c + sbase, iters, eps2, rout2, fp);
                 else if (act0)
-                    cell_tile<R, QUAD, CHECK_K, false>(q, s_c + sbase, iters, eps2, rout2, fp);
+                    cell_tile<R, QUAD, CHECK_K, false, kUnroll>(q, s_c + sbase, iters, eps2, rout2, fp);
                 fold(iters, t0 + kTile >= ce);
             }
         }
@@ -440,7 +492,8 @@ __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 4 : 5))) void k_force(
         // ---- reduce the slices of each particle in FP64 (fixed order), write ----
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            if (!(k == 0 ? act0 : act1)) continue;
+            if (!(k == 0 ? act0 : act1) || (SPLIT && sizeof(R) == 4 && fold_to))
+                continue;
             double r0 = q[k].total(0), r1 = q[k].total(1), r2 = q[k].total(2),
                    r3 = q[k].total(3);
             for (int d = nw; d < kWave; d <<= 1) {
@@ -449,7 +502,11 @@ __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 4 : 5))) void k_force(
                 r2 += __shfl_xor(r2, d, kWave);
                 r3 += __shfl_xor(r3, d, kWave);
             }
-            if (slice == 0 && q[k].i >= 0) {
+            if (SPLIT && sizeof(R) == 8 && fold_to) {   // a split group: [part][member]
+                if (slice == 0 && q[k].i >= 0)
+                    fold_to[(int64_t)wi.part * gi.count + (q[k].i - gi.first)] =
+                        Part<R>{(R)r0, (R)r1, (R)r2, (R)r3};
+            } else if (slice == 0 && q[k].i >= 0) {
                 const int64_t o = perm[q[k].i];
                 acc[3 * o] = r0;
                 acc[3 * o + 1] = r1;
@@ -457,6 +514,64 @@ __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 4 : 5))) void k_force(
                 if (pot) pot[o] = r3;
             }
         }
+    }
+}
+
+// The parts of split group order[blockIdx.x], added up.  FP64: the parts' sums
+// of each member, in order.  FP32: the partial sums of each lane in list
+// order, compensated, as k_force folds those of a whole group (the same bits),
+// then the slices in FP64.
+template <class R>
+__global__ __launch_bounds__(kForceThreads) void k_force_fold(
+    const GroupInfo *__restrict__ grp, ListsDev L, const SplitGroup *__restrict__ sg,
+    const Part<R> *__restrict__ part,
+    const int32_t *__restrict__ perm, double *__restrict__ acc, double *__restrict__ pot) {
+    const int g = L.order[blockIdx.x];
+    const int parts = sg[g].parts;
+    if (parts == 1) return;   // its lists are whole
+    const GroupInfo gi = grp[g];
+    const Part<R> *src = part + sg[g].base;
+    auto store = [&](int li, double r0, double r1, double r2, double r3) {
+        const int64_t o = perm[gi.first + li];
+        acc[3 * o] = r0;
+        acc[3 * o + 1] = r1;
+        acc[3 * o + 2] = r2;
+        if (pot) pot[o] = r3;
+    };
+    if (sizeof(R) == 8) {
+        for (int li = threadIdx.x; li < gi.count; li += kForceThreads) {
+            double r[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+            for (int p = 0; p < parts; ++p) {
+                const Part<R> t = src[(int64_t)p * gi.count + li];
+                r[0] += t.ax; r[1] += t.ay; r[2] += t.az; r[3] += t.ph;
+            }
+            store(li, r[0], r[1], r[2], r[3]);
+        }
+        return;
+    }
+    const int lane = threadIdx.x % kWave;
+    const int ls = choose_log2_slices(gi.count, 2 * kForceWaves);
+    const int nw = kWave >> ls, V = (gi.count + nw - 1) / nw;
+    const int64_t ul = (int64_t)kTile * fold_tiles(ls);
+    int64_t units = 0;
+    for (int k = 0; k < 3; ++k) units += (L.end[k][g] - L.beg[k][g] + ul - 1) / ul;
+    for (int v = threadIdx.x / kWave; v < V; v += kForceWaves) {
+        const Part<R> *p = src + v * kWave + lane;
+        Sum<R> sx, sy, sz, sp;
+#pragma unroll 4
+        for (int64_t u = 0; u < units; ++u, p += V * kWave) {
+            const Part<R> t = *p;
+            sx.add(t.ax); sy.add(t.ay); sz.add(t.az); sp.add(t.ph);
+        }
+        double r0 = sx.value(), r1 = sy.value(), r2 = sz.value(), r3 = sp.value();
+        for (int d = nw; d < kWave; d <<= 1) {
+            r0 += __shfl_xor(r0, d, kWave);
+            r1 += __shfl_xor(r1, d, kWave);
+            r2 += __shfl_xor(r2, d, kWave);
+            r3 += __shfl_xor(r3, d, kWave);
+        }
+        if (lane < nw && v * nw + lane < gi.count) store(v * nw + lane, r0, r1, r2, r3);
     }
 }
 
@@ -477,8 +592,26 @@ static ForceParams force_params(const p3t_ctx *ctx) {
 
 template <class R, bool QUAD, bool CHECK_K>
 static void launch_force_t(p3t_ctx *ctx, const ForceParams &fp, double *acc, double *pot) {
-    k_force<R, QUAD, CHECK_K><<<(unsigned)ctx->n_groups, kForceThreads, 0, ctx->stream>>>(
-        ptr<GroupInfo>(ctx->grp), lists_dev(ctx), ptr<PosMass>(ctx->xm), ptr<NodeMP>(ctx->node_mp), ptr<int32_t>(ctx->vals[0]), fp, acc, pot);
+    const GroupInfo *grp = ptr<GroupInfo>(ctx->grp);
+    const ListsDev L = lists_dev(ctx);
+    const int32_t *perm = ptr<int32_t>(ctx->vals[0]);
+    const SplitGroup *sg = split_groups(ctx);
+    Part<R> *part = ptr<Part<R>>(ctx->fpart);
+    auto launch = [&](auto kernel, int64_t blocks) {
+        if (blocks > 0)
+            kernel<<<(unsigned)blocks, kForceThreads, 0, ctx->stream>>>(
+                grp, L, work_dev(ctx), sg, part, ptr<PosMass>(ctx->xm), ptr<NodeMP>(ctx->node_mp),
+                perm, fp, acc, pot);
+    };
+    if constexpr (sizeof(R) == 8) {
+        launch(k_force<R, QUAD, CHECK_K, true>, work_blocks(ctx));
+    } else {
+        launch(k_force<R, QUAD, CHECK_K, true>, ctx->n_items);
+        launch(k_force<R, QUAD, CHECK_K, false>, ctx->n_groups - ctx->n_split);
+    }
+    if (ctx->n_split > 0)
+        k_force_fold<R><<<(unsigned)ctx->n_split, kForceThreads, 0, ctx->stream>>>(
+            grp, L, sg, part, perm, acc, pot);
 }
 
 template <class R>

@@ -11,6 +11,7 @@ namespace p3t {
 
 constexpr int kMaxLevel = 21;        // 63-bit keys, 3 bits per level
 constexpr int kLevels = kMaxLevel + 1;
+constexpr int kOrderBins = 128;      // launch-order buckets of the groups (walk.hip)
 
 // Root cube of the last build (device resident).
 struct RootInfo {
@@ -106,7 +107,7 @@ struct p3t_ctx {
     unsigned long long nbr_tag = 0;   // number of neighbour searches so far (tags their readback words)
     double ms_build = 0, ms_walk = 0, ms_force = 0, ms_nbr = 0, ms_vjp = 0;
     hipEvent_t ev[12] = {nullptr};  // start/end pairs: build, force, neighbours, vjp, walk, hermite
-    int64_t *hpin = nullptr;      // pinned host readback area (64 int64)
+    int64_t *hpin = nullptr;      // pinned host readback area (kReadbackWords int64)
     void *scratch = nullptr;      // device address of the library's static workspace on this device
 
     p3t::DevBuf root, keys[2], vals[2], hist, histc, rs_tot, xm, xm_in;
@@ -117,7 +118,12 @@ struct p3t_ctx {
     p3t::DevBuf cnt, off, c_idx, p_idx, n_idx;
     p3t::DevBuf wstack, readback, scan_tmp, nbr_cnt, nbr_slots, nbr_scan;
     p3t::DevBuf vjp_gx, vjp_gm, vjp_cell, bbox;
-    p3t::DevBuf seg_end, gorder, grank, ghist;
+    p3t::DevBuf seg_end, gorder, grank;
+    // Work items of the interaction and adjoint kernels (walk.hip): the items
+    // of the n_split first groups of the launch order in [0, n_items) of `work`
+    // (the device holds how many there are), then one item per other group.
+    int64_t n_split = 0, n_items = 0;
+    p3t::DevBuf work, fpart;           // items and split groups; partial sums
     p3t::DevBuf hard_ix, hard_state;   // hard part: components and integrator state
     p3t::DevBuf hard_giant;            // ... and the step bookkeeping of the largest components
     // the hard part's concurrent classes (aux_streams); the neighbour search
@@ -140,7 +146,7 @@ namespace p3t {
 int ensure(p3t_ctx *ctx, DevBuf &b, size_t bytes);
 // The device readback area (kReadbackWords int64 words), allocated and cleared
 // on first use.
-constexpr int kReadbackWords = 64;
+constexpr int kReadbackWords = 640;
 int ensure_readback(p3t_ctx *ctx);
 void release(p3t_ctx *ctx, DevBuf &b);
 int set_error(p3t_ctx *ctx, int status, const char *fmt, ...);
@@ -164,9 +170,10 @@ int scan_rows_i32(p3t_ctx *ctx, const int32_t *in, int32_t *out, int32_t *totals
 // build: the node count of each level (kLevels int32), then the input check.
 constexpr int kRbTopoBad = kLevels + 1;
 // The walk's statistics from this slot on (kRbWalkWords words, cleared by the
-// group selection before every walk of a build).
-constexpr int kRbWalk = 24;
-constexpr int kRbWalkWords = 13;
+// moments of the leaves before every walk of a build).
+constexpr int kRbWalk = 64;
+constexpr int kRbWalkWords = 16 + 4 * kOrderBins;
+static_assert(kRbWalk + kRbWalkWords <= kReadbackWords, "readback layout");
 
 // Tree build stages (tree.hip).
 // root cube, Morton keys, stable sort (keys[0] / vals[0]) and the sorted
@@ -180,6 +187,57 @@ int build_groups(p3t_ctx *ctx);                 // sets ctx->n_groups
 // stats_cleared: the walk's statistics slots are already zero (a build clears
 // them in the group selection); a walk after p3t_release_lists clears them.
 int build_lists(p3t_ctx *ctx, bool stats_cleared);
+
+// One block's work: part `part` of `parts` of group g's lists, for the virtual
+// wavefronts of round `round` (-1: every round, a group that is not split).
+struct WorkItem {
+    int32_t g, part, parts, round;
+};
+struct WorkDev {
+    const WorkItem *items;
+    const int32_t *n_split_items;   // items in front of first_whole
+    int32_t first_whole;            // from here on, whole groups
+};
+// a split group's first partial sum, and the parts its lists are cut into
+struct SplitGroup {
+    int32_t base, parts;
+};
+WorkDev work_dev(const p3t_ctx *ctx);
+SplitGroup *split_groups(const p3t_ctx *ctx);   // [n_groups], in the items' buffer
+inline int64_t work_blocks(const p3t_ctx *ctx) {
+    return ctx->n_items + ctx->n_groups - ctx->n_split;
+}
+
+// Units [lo, hi) of a list of units: those that start in this part, with the
+// lists laid end to end (far, near, cells) and weighted by their cost per entry.
+struct PartRange {
+    int64_t lo[3], hi[3];           // by list: cells, far, near
+};
+__device__ __forceinline__ PartRange part_range(const int64_t n[3], int part, int parts) {
+    PartRange r;
+    if (parts == 1) {
+        for (int k = 0; k < 3; ++k) {
+            r.lo[k] = 0;
+            r.hi[k] = n[k];
+        }
+        return r;
+    }
+    const int64_t w[3] = {7, 3, 6};
+    const int64_t total = w[0] * n[0] + w[1] * n[1] + w[2] * n[2];
+    const int64_t a = total * part / parts, b = total * (part + 1) / parts;
+    int64_t at = 0;
+    for (int q = 0; q < 3; ++q) {
+        const int k = q == 2 ? 0 : q + 1;
+        auto first = [&](int64_t x) {
+            const int64_t u = x <= at ? 0 : (x - at + w[k] - 1) / w[k];
+            return u < n[k] ? u : n[k];
+        };
+        r.lo[k] = first(a);
+        r.hi[k] = first(b);
+        at += w[k] * n[k];
+    }
+    return r;
+}
 
 // Interactions (force.hip).
 int launch_force(p3t_ctx *ctx, double *acc, double *pot);

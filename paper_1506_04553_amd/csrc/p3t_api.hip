@@ -179,7 +179,8 @@ extern "C" int p3t_create(p3t_ctx **out, int device, void *hip_stream, p3t_alloc
     }
     // coherent: some kernels write their few result words straight into it,
     // read by the host after the stream's synchronisation
-    hipError_t e = hipHostMalloc((void **)&ctx->hpin, 64 * sizeof(int64_t), hipHostMallocCoherent);
+    hipError_t e = hipHostMalloc((void **)&ctx->hpin, kReadbackWords * sizeof(int64_t),
+                                 hipHostMallocCoherent);
     for (int k = 0; k < 12 && e == hipSuccess; ++k) e = hipEventCreate(&ctx->ev[k]);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_lists, hipEventDisableTiming);
     for (int k = 0; k < 2 && e == hipSuccess; ++k)
@@ -205,7 +206,7 @@ extern "C" void p3t_destroy(p3t_ctx *ctx) {
                       &ctx->gscan, &ctx->grp, &ctx->cnt, &ctx->off, &ctx->c_idx, &ctx->p_idx,
                       &ctx->n_idx, &ctx->wstack, &ctx->readback, &ctx->scan_tmp,
                       &ctx->nbr_cnt, &ctx->nbr_slots, &ctx->nbr_scan, &ctx->vjp_gx, &ctx->vjp_gm, &ctx->vjp_cell, &ctx->bbox,
-                      &ctx->seg_end, &ctx->gorder, &ctx->grank, &ctx->ghist, &ctx->hard_ix,
+                      &ctx->seg_end, &ctx->gorder, &ctx->grank, &ctx->work, &ctx->fpart, &ctx->hard_ix,
                       &ctx->hard_state, &ctx->step_off, &ctx->step_idx, &ctx->step_off2,
                       &ctx->step_idx2, &ctx->kinds_cnt, &ctx->hard_giant};
     for (DevBuf *b : bufs) release(ctx, *b);

@@ -929,7 +929,7 @@ __global__ __launch_bounds__(128) void k_moments_leaves(MomentArrays A, int32_t 
                                                         int32_t *__restrict__ parent,
                                                         LevelStarts ls) {
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id < kRbWalkWords) A.walk_zero[id] = 0;
+    for (int64_t k = id; k < kRbWalkWords; k += (int64_t)gridDim.x * blockDim.x) A.walk_zero[k] = 0;
     if (id >= A.n_nodes) return;
     if (id == 0) parent[0] = -1;
     if (nchild[id] != 0) {

@@ -212,37 +212,110 @@ struct WalkStats {
     unsigned long long n_leaves;
     unsigned long long maxlen[3];  // longest list of each kind
     int32_t stack_ovf, cap_ovf;    // flags written by the walk
-    int32_t spilled, pad;          // groups that needed the global stack
+    int32_t spilled, n_items;      // groups that needed the global stack; items of split groups
+    unsigned long long part_used;  // partial sums handed out to split groups
+    unsigned long long pad[2];
+    // per launch-order bucket (see below): groups, their cost, and what their
+    // partial sums would take if they were split (FP32: exactly; FP64: members
+    // times cost)
+    unsigned long long bin[kOrderBins], bin_cost[kOrderBins], bin_room[kOrderBins];
+    unsigned long long bin_rounds[kOrderBins];   // rounds of the interaction kernel
 };
 
 static_assert(sizeof(WalkStats) == kRbWalkWords * 8, "walk statistics slots");
 
-constexpr int kOrderBins = 128;   // launch-order buckets (see below)
+// ---------------------------------------------------------------------------
+// Launch order of the per-group kernels: groups in buckets of estimated work
+// (quarter octaves of n_g (35 |C_g| + 15 |P_g|), the interaction kernel's
+// instruction count), largest first; the order inside a bucket is arbitrary
+// (it decides only which block runs which group).
+// ---------------------------------------------------------------------------
+__host__ __device__ __forceinline__ int cost_bin(float cost) {
+    int b = (int)(4.0f * log2f(cost + 1.0f));
+    b = b < 0 ? 0 : (b > kOrderBins - 1 ? kOrderBins - 1 : b);
+    return kOrderBins - 1 - b;
+}
 
-// Statistics from the per-group counts, and the leaf count of the tree; also
-// clears the launch-order bucket counts.
+__device__ __forceinline__ float group_cost(int ng, int64_t c, int64_t p) {
+    return (float)ng * (35.0f * (float)c + 15.0f * (float)p);
+}
+
+// a group's 256-entry tiles per list in units of `tiles` tiles
+__device__ __forceinline__ int64_t units_of(int64_t entries, int tiles) {
+    return (entries + 256 * tiles - 1) / (256 * tiles);
+}
+
+// rounds of 8 virtual wavefronts over a split group's lists
+__device__ __forceinline__ int rounds_of(int ng, bool wide) {
+    const int nw = kWave >> (wide ? fill_log2_slices(ng) : choose_log2_slices(ng, 8));
+    return ((ng + nw - 1) / nw + 7) / 8;
+}
+
+// FP32: the partial sums of a split group, one per unit, virtual wavefront and lane
+__device__ __forceinline__ int64_t fp32_room(int ng, int64_t c, int64_t f, int64_t n) {
+    const int ls = choose_log2_slices(ng, 8), nw = kWave >> ls, t = fold_tiles(ls);
+    return (units_of(c, t) + units_of(f, t) + units_of(n, t)) * ((ng + nw - 1) / nw) * kWave;
+}
+
+// Statistics from the per-group counts, the leaf count of the tree, and the
+// launch-order buckets: each group's bucket and rank in it (rank[g], packed in
+// 8 + 24 bits; not written when G does not fit), the bucket counts gathered in
+// LDS first, so that a bucket sees one global update per block.
 __global__ __launch_bounds__(1024) void k_walk_stats(const GroupInfo *__restrict__ grp,
                                                     const int32_t *__restrict__ n_groups_dev,
                                                     const int64_t *__restrict__ cnt, int64_t S,
                                                     const int32_t *__restrict__ nchild,
-                                                    int64_t n_nodes, WalkStats *__restrict__ out,
-                                                    uint32_t *__restrict__ order_hist) {
+                                                    int64_t n_nodes, bool wide,
+                                                    WalkStats *__restrict__ out,
+                                                    int32_t *__restrict__ rank) {
+    __shared__ unsigned long long s_cost[kOrderBins], s_room[kOrderBins], s_rounds[kOrderBins];
+    __shared__ uint32_t s_bin[kOrderBins];
     const int G = *n_groups_dev;
+    const bool ranks = G < (1 << 24);
+    if (threadIdx.x < kOrderBins) {
+        s_bin[threadIdx.x] = 0;
+        s_cost[threadIdx.x] = s_room[threadIdx.x] = s_rounds[threadIdx.x] = 0;
+    }
+    __syncthreads();
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t0 < kOrderBins) order_hist[t0] = 0;
     const int64_t nt = (int64_t)gridDim.x * blockDim.x;
     unsigned long long tot[3] = {0, 0, 0}, mx[3] = {0, 0, 0}, pc = 0, pp = 0, ppn = 0, lv = 0;
     for (int64_t g = t0; g < G; g += nt) {
-        const unsigned long long n = (unsigned long long)grp[g].count;
+        const int ng = grp[g].count;
+        const unsigned long long n = (unsigned long long)ng;
+        int64_t c[3];
         for (int k = 0; k < 3; ++k) {
-            const unsigned long long c = cnt[k * S + g];
-            tot[k] += c;
-            mx[k] = c > mx[k] ? c : mx[k];
+            c[k] = cnt[k * S + g];
+            tot[k] += c[k];
+            mx[k] = (unsigned long long)c[k] > mx[k] ? c[k] : mx[k];
         }
-        pc += n * cnt[g];
-        pp += n * (cnt[S + g] + cnt[2 * S + g]);
-        ppn += n * cnt[2 * S + g];
+        pc += n * c[0];
+        pp += n * (c[1] + c[2]);
+        ppn += n * c[2];
+        if (ranks) {
+            const float cost = group_cost(ng, c[0], c[1] + c[2]);
+            const int b = cost_bin(cost);
+            atomicAdd(&s_cost[b], (unsigned long long)cost);
+            atomicAdd(&s_room[b], wide ? n * (unsigned long long)cost
+                                       : (unsigned long long)fp32_room(ng, c[0], c[1], c[2]));
+            atomicAdd(&s_rounds[b], (unsigned long long)rounds_of(ng, wide));
+            rank[g] = (b << 24) | (int32_t)atomicAdd(&s_bin[b], 1u);
+        }
     }
+    __syncthreads();
+    if (threadIdx.x < kOrderBins && s_bin[threadIdx.x]) {
+        s_bin[threadIdx.x] =
+            (uint32_t)atomicAdd(&out->bin[threadIdx.x], (unsigned long long)s_bin[threadIdx.x]);
+        atomicAdd(&out->bin_cost[threadIdx.x], s_cost[threadIdx.x]);
+        atomicAdd(&out->bin_room[threadIdx.x], s_room[threadIdx.x]);
+        atomicAdd(&out->bin_rounds[threadIdx.x], s_rounds[threadIdx.x]);
+    }
+    __syncthreads();
+    if (ranks)   // this block's groups come after those already counted
+        for (int64_t g = t0; g < G; g += nt) {
+            const int32_t r = rank[g];
+            rank[g] = r + (int32_t)s_bin[r >> 24];
+        }
     for (int64_t i = t0; i < n_nodes; i += nt) lv += nchild[i] == 0;
     // wave reductions, then one set of updates per block
     __shared__ unsigned long long s_red[16][10];
@@ -293,93 +366,198 @@ ListsDev lists_dev(const p3t_ctx *ctx) {
     return L;
 }
 
-// ---------------------------------------------------------------------------
-// Launch order of the per-group kernels: groups in buckets of estimated work
-// (quarter octaves of n_g (35 |C_g| + 15 |P_g|), the interaction kernel's
-// instruction count), largest first; the order inside a bucket is arbitrary
-// (it decides only which block runs which group).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ int order_bin(const GroupInfo &gi, const int64_t *cnt, int64_t S, int g) {
-    const float cost = (float)gi.count * (35.0f * (float)cnt[g] +
-                                          15.0f * (float)(cnt[S + g] + cnt[2 * S + g]));
-    int b = (int)(4.0f * log2f(cost + 1.0f));
-    b = b < 0 ? 0 : (b > kOrderBins - 1 ? kOrderBins - 1 : b);
-    return kOrderBins - 1 - b;
-}
+// What splits: the groups of the first buckets, into parts of about `share`.
+struct SplitPlan {
+    int last_bin;          // groups of buckets 0 .. last_bin are split (-1: none)
+    int first_whole;       // work items kept for them
+    bool wide;             // FP64
+    float share;
+    int64_t room;          // partial sums there is room for
+    int32_t *n_items;      // device counters, zero before the launch
+    unsigned long long *used;
+    SplitGroup *group;     // [G], written for the groups of the split buckets
+    WorkItem *work;
+};
+constexpr int kMaxParts = 256;
 
-// bucket counts (one atomic per bucket and wavefront) and each group's rank in its bucket
-__global__ __launch_bounds__(256) void k_order_count(const GroupInfo *__restrict__ grp, int64_t G,
-                                                     const int64_t *__restrict__ cnt, int64_t S,
-                                                     uint32_t *__restrict__ hist,
-                                                     int32_t *__restrict__ rank) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = g < G;
-    const int b = valid ? order_bin(grp[g], cnt, S, (int)g) : 0;
-    uint64_t same = ballot(valid);
-#pragma unroll
-    for (int k = 0; k < 7; ++k) {
-        const bool bit = (b >> k) & 1;
-        const uint64_t bb = ballot(bit);
-        same &= bit ? bb : ~bb;
-    }
-    const int leader = valid ? __ffsll((long long)same) - 1 : 0;
-    uint32_t base = 0;
-    if (valid && lane_id() == leader) base = atomicAdd(&hist[b], (uint32_t)__popcll(same));
-    base = __shfl(base, leader, kWave);
-    if (valid) rank[g] = (b << 24) | (int32_t)(base + count_below(same));
-}
-
-// each block takes the bucket starts (exclusive scan of the counts) itself
+// Group order from the ranks, and the work items: each block takes the bucket
+// starts (exclusive scan of the counts) itself.  A group of the split buckets
+// becomes one item per round and part, with up to one part per unit of its
+// lists; if the partial sums' room is used up its lists stay whole.
 __global__ __launch_bounds__(256) void k_order_place(int64_t G, const int32_t *__restrict__ rank,
-                                                     const uint32_t *__restrict__ hist,
-                                                     int32_t *__restrict__ order) {
+                                                     const unsigned long long *__restrict__ bins,
+                                                     int32_t *__restrict__ order,
+                                                     const GroupInfo *__restrict__ grp,
+                                                     const int64_t *__restrict__ cnt, int64_t S,
+                                                     SplitPlan sp) {
     static_assert(kOrderBins <= 256, "one thread per bucket");
-    __shared__ uint32_t s_cnt[kOrderBins], s_start[kOrderBins];
+    __shared__ uint32_t s_cnt[kOrderBins], s_start[kOrderBins + 1];
     const int t = threadIdx.x;
-    if (t < kOrderBins) s_cnt[t] = hist[t];
+    if (t < kOrderBins) s_cnt[t] = (uint32_t)bins[t];
     __syncthreads();
     if (t < kOrderBins) {
         uint32_t e = 0;
         for (int k = 0; k < t; ++k) e += s_cnt[k];
         s_start[t] = e;
+        if (t == kOrderBins - 1) s_start[kOrderBins] = e + s_cnt[t];
     }
     __syncthreads();
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + t;
-    if (g >= G) return;
-    const int32_t r = rank[g];
-    order[s_start[r >> 24] + (r & 0xffffff)] = (int32_t)g;
+    const int32_t r = g < G ? rank[g] : 0;
+    const int bin = r >> 24;
+    const uint32_t pos = s_start[bin] + (r & 0xffffff);
+    const bool split = g < G && bin <= sp.last_bin;
+    if (g < G) {
+        order[pos] = (int32_t)g;
+        if (!split)
+            sp.work[sp.first_whole + pos - s_start[sp.last_bin + 1]] = WorkItem{(int32_t)g, 0, 1, -1};
+    }
+    uint64_t todo = ballot(split);
+    if (!todo) return;
+    int parts = 0, rounds = 0;
+    int64_t room = 0;
+    if (split) {
+        const int ng = grp[g].count;
+        const int64_t c = cnt[g], f = cnt[S + g], n = cnt[2 * S + g];
+        const int tiles = sp.wide ? 1 : fold_tiles(choose_log2_slices(ng, 8));
+        const int64_t units = units_of(c, tiles) + units_of(f, tiles) + units_of(n, tiles);
+        rounds = rounds_of(ng, sp.wide);
+        const int64_t want = (int64_t)ceilf(group_cost(ng, c, f + n) / (sp.share * (float)rounds));
+        parts = (int)min<int64_t>(min<int64_t>(want, units), kMaxParts);
+        if (parts < 1) parts = 1;
+        room = parts == 1 ? 0 : sp.wide ? (int64_t)parts * ng : fp32_room(ng, c, f, n);
+    }
+    const int64_t rincl = wave_incl_scan(room);
+    int64_t rbase = 0;
+    if (lane_id() == kWave - 1) rbase = (int64_t)atomicAdd(sp.used, (unsigned long long)rincl);
+    rbase = __shfl(rbase, kWave - 1, kWave) + rincl - room;
+    if (rbase + room > sp.room) parts = split ? 1 : 0;
+    const int incl = wave_incl_scan(parts * rounds);
+    int32_t base = 0;
+    if (lane_id() == kWave - 1) base = atomicAdd(sp.n_items, incl);
+    base = __shfl(base, kWave - 1, kWave) + incl - parts * rounds;
+    if (split) sp.group[g] = SplitGroup{(int32_t)rbase, parts};
+    while (todo) {   // the wavefront writes one group's items after another
+        const int src = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int np = __shfl(parts, src, kWave), nr = __shfl(rounds, src, kWave);
+        const int b = __shfl(base, src, kWave);
+        const int32_t gs = __shfl((int32_t)g, src, kWave);
+        for (int q = lane_id(); q < np * nr; q += kWave)
+            sp.work[b + q] = WorkItem{gs, q % np, np, q / np};
+    }
 }
 
-__global__ void k_order_identity(int64_t G, int32_t *__restrict__ order) {
+__global__ void k_order_identity(int64_t G, int32_t *__restrict__ order,
+                                 WorkItem *__restrict__ work) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g < G) order[g] = (int32_t)g;
+    if (g >= G) return;
+    order[g] = (int32_t)g;
+    work[g] = WorkItem{(int32_t)g, 0, 1, -1};
+}
+
+static WalkStats *walk_stats_dev(const p3t_ctx *ctx) {
+    return reinterpret_cast<WalkStats *>(ptr<int64_t>(ctx->readback) + kRbWalk);
+}
+static const WalkStats *walk_stats_host(const p3t_ctx *ctx) {
+    return reinterpret_cast<const WalkStats *>(ctx->hpin + kRbWalk);
+}
+SplitGroup *split_groups(const p3t_ctx *ctx) {
+    return reinterpret_cast<SplitGroup *>(ptr<WorkItem>(ctx->work) + work_blocks(ctx));
+}
+
+WorkDev work_dev(const p3t_ctx *ctx) {
+    return WorkDev{ptr<WorkItem>(ctx->work), &walk_stats_dev(ctx)->n_items, (int32_t)ctx->n_items};
+}
+
+// Which groups are split, from the bucket totals in the host's copy of the
+// statistics.  A launch of one block per group ends when its largest group
+// does: few particles make few groups, and a group at the cluster's edge has a
+// wide box that opens almost every cell.  In FP64, groups above a share of the
+// work of the blocks that run at once are cut into parts of that size, in the
+// same launch: a quarter of an even share where the groups are few (Plummer
+// 65536, Salpeter, 1734 groups: 0.90 ms unsplit, 0.56 at half a share, 0.51 at
+// a quarter; Plummer 4096: 155 and 29 us), a whole one where they are many and
+// only the largest stand out (King 500009, 6818 groups: 2.55 ms unsplit, 2.61
+// at a quarter).  FP32 has a launch of its own for the parts, before the whole
+// groups', which costs more than it gains unless every group goes there, where
+// they are too few to fill the GPU (Plummer 1000: 86 us unsplit, 44 split;
+// Plummer 2^18, n_crit 128: 0.80 ms unsplit, 0.99 with the groups above half
+// a share split).
+constexpr int kBlocks64 = 256 * 4, kBlocks32 = 256 * 5;   // blocks in flight on 256 CUs
+constexpr int kFewGroups64 = 2 * kBlocks64;
+constexpr int64_t kSplitScratch = (int64_t)256 << 20;    // bound on the partial sums' bytes
+static int plan_split(p3t_ctx *ctx, SplitPlan &sp) {
+    int rc;
+    const WalkStats *hs = walk_stats_host(ctx);
+    const bool wide = ctx->prm.precision == P3T_PREC_FP64;
+    sp = SplitPlan{-1, 0, wide, 1.0f, 0, nullptr, nullptr, nullptr, nullptr};
+    const double cost = 35.0 * (double)hs->pc + 15.0 * (double)hs->pp;
+    const double share =
+        cost / (wide ? (ctx->n_groups <= kFewGroups64 ? 4.0 : 1.0) * kBlocks64 : 2.0 * kBlocks32) + 1.0;
+    const int last = wide ? cost_bin((float)share)
+                          : ctx->n_groups <= kBlocks32 ? kOrderBins - 1 : -1;
+    int64_t groups = 0, rounds = 0;
+    double work = 0.0, room = 0.0;
+    for (int b = 0; b <= last; ++b) {
+        groups += (int64_t)hs->bin[b];
+        work += (double)hs->bin_cost[b];
+        room += (double)hs->bin_room[b];
+        rounds += (int64_t)hs->bin_rounds[b];
+    }
+    // each group: at most cost / share + rounds (and rounding of the sums)
+    const int64_t items = groups ? (int64_t)(work / share * 1.0001) + groups + rounds : 0;
+    const size_t one = 4 * (wide ? sizeof(double) : sizeof(float));
+    // FP64: a group of n members and p <= cost / share + 1 parts takes n p sums
+    if (wide) room = room / share + (double)ctx->n;
+    if (room * (double)one > (double)kSplitScratch) room = (double)(kSplitScratch / one);
+    if (groups) {
+        sp.last_bin = last;
+        sp.first_whole = (int)items;
+        sp.share = (float)share;
+        sp.room = (int64_t)room;
+        if ((rc = ensure(ctx, ctx->fpart, (size_t)sp.room * one))) return rc;
+        sp.n_items = &walk_stats_dev(ctx)->n_items;
+        sp.used = &walk_stats_dev(ctx)->part_used;
+    }
+    ctx->n_split = groups;
+    ctx->n_items = items;
+    // the items, then each group's first partial sum and parts
+    const int64_t blocks = work_blocks(ctx);
+    if ((rc = ensure(ctx, ctx->work,
+                     (size_t)blocks * sizeof(WorkItem) + (size_t)ctx->n_groups * sizeof(SplitGroup))))
+        return rc;
+    sp.work = ptr<WorkItem>(ctx->work);
+    sp.group = split_groups(ctx);
+    return P3T_OK;
 }
 
 static int build_order(p3t_ctx *ctx, int64_t stride) {
     int rc;
     const int64_t G = ctx->n_groups;
     if ((rc = ensure(ctx, ctx->gorder, (G + 1) * sizeof(int32_t)))) return rc;
-    if ((rc = ensure(ctx, ctx->grank, (G + 1) * sizeof(int32_t)))) return rc;
+    ctx->n_split = ctx->n_items = 0;
     if (G <= 0) return P3T_OK;
     if (G >= (1 << 24)) {   // ranks are packed in 24 bits: keep the group order
-        k_order_identity<<<blocks_for(G, 256), 256, 0, ctx->stream>>>(G, ptr<int32_t>(ctx->gorder));
+        if ((rc = ensure(ctx, ctx->work, (size_t)G * sizeof(WorkItem)))) return rc;
+        k_order_identity<<<blocks_for(G, 256), 256, 0, ctx->stream>>>(G, ptr<int32_t>(ctx->gorder),
+                                                                     ptr<WorkItem>(ctx->work));
         return check_hip(ctx, hipGetLastError(), "group order");
     }
-    // the bucket counts were cleared by the walk statistics
-    uint32_t *hist = ptr<uint32_t>(ctx->ghist);
-    k_order_count<<<blocks_for(G, 256), 256, 0, ctx->stream>>>(
-        ptr<GroupInfo>(ctx->grp), G, ptr<int64_t>(ctx->cnt), stride, hist, ptr<int32_t>(ctx->grank));
-    k_order_place<<<blocks_for(G, 256), 256, 0, ctx->stream>>>(G, ptr<int32_t>(ctx->grank), hist,
-                                                              ptr<int32_t>(ctx->gorder));
+    SplitPlan sp;
+    if ((rc = plan_split(ctx, sp))) return rc;
+    k_order_place<<<blocks_for(G, 256), 256, 0, ctx->stream>>>(
+        G, ptr<int32_t>(ctx->grank), walk_stats_dev(ctx)->bin, ptr<int32_t>(ctx->gorder),
+        ptr<GroupInfo>(ctx->grp), ptr<int64_t>(ctx->cnt), stride, sp);
     return check_hip(ctx, hipGetLastError(), "group order");
 }
 
 static int run_walk_stats(p3t_ctx *ctx, const int32_t *G_dev, int64_t stride, WalkStats *ws) {
     // few large blocks: the block results meet in same-address atomics
-    k_walk_stats<<<32, 1024, 0, ctx->stream>>>(ptr<GroupInfo>(ctx->grp), G_dev,
-                                              ptr<int64_t>(ctx->cnt), stride,
-                                              ptr<int32_t>(ctx->node_nchild), ctx->n_nodes, ws,
-                                              ptr<uint32_t>(ctx->ghist));
+    k_walk_stats<<<32, 1024, 0, ctx->stream>>>(
+        ptr<GroupInfo>(ctx->grp), G_dev, ptr<int64_t>(ctx->cnt), stride,
+        ptr<int32_t>(ctx->node_nchild), ctx->n_nodes, ctx->prm.precision == P3T_PREC_FP64, ws,
+        ptr<int32_t>(ctx->grank));
     int rc = check_hip(ctx, hipGetLastError(), "walk stats");
     if (rc) return rc;
     if ((rc = check_hip(ctx, hipMemcpyAsync(ctx->hpin + kRbWalk, ws, sizeof(WalkStats),
@@ -396,19 +574,17 @@ static int lists_done(p3t_ctx *ctx, int rc) {
 }
 
 int build_lists(p3t_ctx *ctx, bool stats_cleared) {
-    static_assert(kRbWalk * 8 + sizeof(WalkStats) <= 40 * 8, "walk readback overlaps other slots");
     int rc;
     const int64_t nn = ctx->n_nodes;   // bound on the number of groups
     const int64_t stride = nn + 1;
     if ((rc = ensure(ctx, ctx->cnt, 3 * stride * sizeof(int64_t)))) return rc;
     if ((rc = ensure(ctx, ctx->off, 3 * stride * sizeof(int64_t)))) return rc;
     if ((rc = ensure(ctx, ctx->seg_end, 3 * stride * sizeof(int64_t)))) return rc;
-    // launch-order bucket counts, cleared by the walk statistics
-    if ((rc = ensure(ctx, ctx->ghist, kOrderBins * sizeof(uint32_t)))) return rc;
+    if ((rc = ensure(ctx, ctx->grank, stride * sizeof(int32_t)))) return rc;
     int64_t *cnt = ptr<int64_t>(ctx->cnt), *off = ptr<int64_t>(ctx->off);
     int64_t *end = ptr<int64_t>(ctx->seg_end);
-    WalkStats *ws = reinterpret_cast<WalkStats *>(ptr<int64_t>(ctx->readback) + kRbWalk);
-    const WalkStats *hs = reinterpret_cast<const WalkStats *>(ctx->hpin + kRbWalk);
+    WalkStats *ws = walk_stats_dev(ctx);
+    const WalkStats *hs = walk_stats_host(ctx);
     const int32_t *G_dev = ptr<int32_t>(ctx->gscan) + ctx->n;
     const double hn = ctx->prm.r_search > ctx->prm.r_out ? ctx->prm.r_search : ctx->prm.r_out;
     const WalkParams wp{ctx->prm.theta * ctx->prm.theta, ctx->prm.r_search * ctx->prm.r_search,
