@@ -119,6 +119,12 @@ __device__ __forceinline__ int fill_log2_slices(int n) {
     return ls;
 }
 
+// Rounds of 8 virtual wavefronts over a split group's lists (wide: FP64).
+__device__ __forceinline__ int rounds_of(int n, bool wide) {
+    const int nw = kWave >> (wide ? fill_log2_slices(n) : choose_log2_slices(n, 8));
+    return ((n + nw - 1) / nw + 7) / 8;
+}
+
 // The 256-entry tiles of a group's lists that make one unit of its interaction
 // kernel: FP32 folds its partial sums into the compensated ones after at least
 // 64 entries per lane, so a unit is the tiles between two folds.

@@ -292,27 +292,45 @@ __device__ __forceinline__ void vjp_i_pp_tile(const VjpPart<R> *sp, const int32_
     }
 }
 
+// This block's share of a group (the work items of the interaction kernel):
+// share `q` of `of`.
+struct VjpShare {
+    int32_t g, q, of;
+};
+template <class R>
+__device__ __forceinline__ bool vjp_share(const GroupInfo *grp, const WorkDev &wd, VjpShare &v) {
+    const int64_t item = blockIdx.x;
+    if (item < wd.first_whole && item >= *wd.n_split_items) return false;
+    const WorkItem wi = wd.items[item];
+    const int rounds = wi.round < 0 ? 1 : rounds_of(grp[wi.g].count, sizeof(R) == 8);
+    v = VjpShare{wi.g, wi.parts * (wi.round < 0 ? 0 : wi.round) + wi.part, wi.parts * rounds};
+    return true;
+}
+
 template <class R>
 __global__ __launch_bounds__(kVjpThreads) void k_vjp_i(
-    const GroupInfo *__restrict__ grp, ListsDev L, const PosMass *__restrict__ xm,
-    const NodeMP *__restrict__ mp,
+    const GroupInfo *__restrict__ grp, ListsDev L, WorkDev wd, const PosMass *__restrict__ xm,
     const int32_t *__restrict__ perm, const double *__restrict__ wv, const double *__restrict__ cv,
     VjpParams vp, double *__restrict__ gx, double *__restrict__ gm, int64_t n) {
     __shared__ VjpPart<R> s_p[kVjpTile];
     __shared__ int32_t s_j[kVjpTile];
     __shared__ double s_red[3][kVjpThreads];
     const int tid = threadIdx.x;
-    const int g = L.order[blockIdx.x];
+    VjpShare share;
+    if (!vjp_share<R>(grp, wd, share)) return;
+    const int g = share.g;
     const GroupInfo gi = grp[g];
     double sh[3];
     group_shift<R>(gi, sh);
     // members in chunks of the largest power of two that fits (at most 256),
     // so that a chunk fills its lanes: 74 members run as 64 + 8 + 2
-    for (int chunk = 0, nc = 0; chunk < gi.count; chunk += nc) {
+    // (each chunk by one of the blocks that share the group)
+    for (int chunk = 0, nc = 0, turn = 0; chunk < gi.count; chunk += nc, ++turn) {
         const int rem = gi.count - chunk;
         int lg = 0;
         while (lg < 8 && (2 << lg) <= rem) ++lg;
         nc = 1 << lg;
+        if (turn % share.of != share.q) continue;
         const int pad = nc, nslice = kVjpThreads >> lg;
         const int li = tid & (pad - 1), slice = tid >> lg;
         const int32_t i = gi.first + chunk + li;
@@ -390,7 +408,7 @@ __device__ __forceinline__ void vjp_scatter_pp(const VjpMember<R> *si, const int
 
 template <class R, bool CELL_K, bool QUAD>
 __global__ __launch_bounds__(kVjpThreads) void k_vjp_scatter(
-    const GroupInfo *__restrict__ grp, ListsDev L, const PosMass *__restrict__ xm,
+    const GroupInfo *__restrict__ grp, ListsDev L, WorkDev wd, const PosMass *__restrict__ xm,
     const NodeMP *__restrict__ mp,
     const int32_t *__restrict__ perm, const double *__restrict__ wv, const double *__restrict__ cv,
     VjpParams vp, double *__restrict__ gx, double *__restrict__ gm, double *__restrict__ cadj,
@@ -400,13 +418,24 @@ __global__ __launch_bounds__(kVjpThreads) void k_vjp_scatter(
     // per wavefront and member: the member's cell terms dl/dr (FP64 partials)
     __shared__ double s_gr[kVjpThreads / kWave][kVjpThreads][3];
     const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
-    const int g = L.order[blockIdx.x];
+    VjpShare share;
+    if (!vjp_share<R>(grp, wd, share)) return;
+    const int g = share.g;
     const GroupInfo gi = grp[g];
     double sh[3];
     group_shift<R>(gi, sh);
-    const int64_t cb = L.beg[0][g], ce = L.end[0][g];
-    const int64_t fb = L.beg[1][g], fe = L.end[1][g];
-    const int64_t nb = L.beg[2][g], ne = L.end[2][g];
+    int64_t cb = L.beg[0][g], ce = L.end[0][g];
+    int64_t fb = L.beg[1][g], fe = L.end[1][g];
+    int64_t nb = L.beg[2][g], ne = L.end[2][g];
+    if (share.of > 1) {   // its tiles of kVjpThreads entries of each list
+        const int64_t t = kVjpThreads;
+        const int64_t tiles[3] = {(ce - cb + t - 1) / t, (fe - fb + t - 1) / t, (ne - nb + t - 1) / t};
+        const PartRange r = part_range(tiles, share.q, share.of);
+        ce = min(ce, cb + r.hi[0] * t); cb += r.lo[0] * t;
+        fe = min(fe, fb + r.hi[1] * t); fb += r.lo[1] * t;
+        ne = min(ne, nb + r.hi[2] * t); nb += r.lo[2] * t;
+        if (cb >= ce && fb >= fe && nb >= ne) return;
+    }
     const int32_t *__restrict__ c_idx = L.idx[0];
     const int32_t *__restrict__ p_idx = L.idx[1];
     const int32_t *__restrict__ n_idx = L.idx[2];
@@ -704,7 +733,9 @@ int launch_vjp_ws(p3t_ctx *ctx, const double *w, const double *c, double *gpos, 
     // caller's graph capture records as an ordinary kernel node)
     k_vjp_zero<<<blocks_for(10 * nn, 256), 256, 0, ctx->stream>>>(10 * nn, cadj);
     if ((rc = check_hip(ctx, hipGetLastError(), "vjp clear"))) return rc;
-    const unsigned G = (unsigned)ctx->n_groups;
+    // a group that the interaction kernel splits is shared by as many blocks here
+    const unsigned blocks = (unsigned)work_blocks(ctx);
+    const WorkDev wd = work_dev(ctx);
     // accepted cells lie at least h from every member: K = W = 1 on them when h >= r_out
     const bool cell_k = ctx->prm.r_search < ctx->prm.r_out;
     // the adjoint terms follow the forward pass's precision
@@ -719,13 +750,13 @@ int launch_vjp_ws(p3t_ctx *ctx, const double *w, const double *c, double *gpos, 
                                       : k_vjp_scatter<double, true, false>)
                               : (quad ? k_vjp_scatter<double, false, true>
                                       : k_vjp_scatter<double, false, false>));
-    ki<<<G, kVjpThreads, 0, ctx->stream>>>(
-        ptr<GroupInfo>(ctx->grp), L, ptr<PosMass>(ctx->xm), ptr<NodeMP>(ctx->node_mp), ptr<int32_t>(ctx->vals[0]), w, c, vp, gx, gm,
-        n);
+    ki<<<blocks, kVjpThreads, 0, ctx->stream>>>(ptr<GroupInfo>(ctx->grp), L, wd,
+                                                ptr<PosMass>(ctx->xm), ptr<int32_t>(ctx->vals[0]),
+                                                w, c, vp, gx, gm, n);
     if ((rc = check_hip(ctx, hipGetLastError(), "vjp i-side"))) return rc;
-    ks<<<G, kVjpThreads, 0, ctx->stream>>>(
-        ptr<GroupInfo>(ctx->grp), L, ptr<PosMass>(ctx->xm), ptr<NodeMP>(ctx->node_mp), ptr<int32_t>(ctx->vals[0]), w, c, vp, gx, gm,
-        cadj, n, nn);
+    ks<<<blocks, kVjpThreads, 0, ctx->stream>>>(
+        ptr<GroupInfo>(ctx->grp), L, wd, ptr<PosMass>(ctx->xm), ptr<NodeMP>(ctx->node_mp),
+        ptr<int32_t>(ctx->vals[0]), w, c, vp, gx, gm, cadj, n, nn);
     if ((rc = check_hip(ctx, hipGetLastError(), "vjp scatter"))) return rc;
     k_vjp_down<<<blocks_for(nn, 128), 128, 0, ctx->stream>>>(
         nn, ptr<int32_t>(ctx->node_nchild), ptr<int32_t>(ctx->node_parent), ptr<NodeMP>(ctx->node_mp),

@@ -245,12 +245,6 @@ __device__ __forceinline__ int64_t units_of(int64_t entries, int tiles) {
     return (entries + 256 * tiles - 1) / (256 * tiles);
 }
 
-// rounds of 8 virtual wavefronts over a split group's lists
-__device__ __forceinline__ int rounds_of(int ng, bool wide) {
-    const int nw = kWave >> (wide ? fill_log2_slices(ng) : choose_log2_slices(ng, 8));
-    return ((ng + nw - 1) / nw + 7) / 8;
-}
-
 // FP32: the partial sums of a split group, one per unit, virtual wavefront and lane
 __device__ __forceinline__ int64_t fp32_room(int ng, int64_t c, int64_t f, int64_t n) {
     const int ls = choose_log2_slices(ng, 8), nw = kWave >> ls, t = fold_tiles(ls);
@@ -390,16 +384,15 @@ __global__ __launch_bounds__(256) void k_order_place(int64_t G, const int32_t *_
                                                      const GroupInfo *__restrict__ grp,
                                                      const int64_t *__restrict__ cnt, int64_t S,
                                                      SplitPlan sp) {
-    static_assert(kOrderBins <= 256, "one thread per bucket");
-    __shared__ uint32_t s_cnt[kOrderBins], s_start[kOrderBins + 1];
+    static_assert(kOrderBins == 2 * kWave, "two buckets per lane");
+    __shared__ uint32_t s_start[kOrderBins + 1];
     const int t = threadIdx.x;
-    if (t < kOrderBins) s_cnt[t] = (uint32_t)bins[t];
-    __syncthreads();
-    if (t < kOrderBins) {
-        uint32_t e = 0;
-        for (int k = 0; k < t; ++k) e += s_cnt[k];
-        s_start[t] = e;
-        if (t == kOrderBins - 1) s_start[kOrderBins] = e + s_cnt[t];
+    if (t < kWave) {
+        const uint32_t a = (uint32_t)bins[2 * t], b = (uint32_t)bins[2 * t + 1];
+        const uint32_t incl = wave_incl_scan(a + b);
+        s_start[2 * t] = incl - a - b;
+        s_start[2 * t + 1] = incl - b;
+        if (t == kWave - 1) s_start[kOrderBins] = incl;
     }
     __syncthreads();
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + t;
@@ -412,8 +405,7 @@ __global__ __launch_bounds__(256) void k_order_place(int64_t G, const int32_t *_
         if (!split)
             sp.work[sp.first_whole + pos - s_start[sp.last_bin + 1]] = WorkItem{(int32_t)g, 0, 1, -1};
     }
-    uint64_t todo = ballot(split);
-    if (!todo) return;
+    if (!ballot(split)) return;
     int parts = 0, rounds = 0;
     int64_t room = 0;
     if (split) {
@@ -437,15 +429,9 @@ __global__ __launch_bounds__(256) void k_order_place(int64_t G, const int32_t *_
     if (lane_id() == kWave - 1) base = atomicAdd(sp.n_items, incl);
     base = __shfl(base, kWave - 1, kWave) + incl - parts * rounds;
     if (split) sp.group[g] = SplitGroup{(int32_t)rbase, parts};
-    while (todo) {   // the wavefront writes one group's items after another
-        const int src = __builtin_ctzll(todo);
-        todo &= todo - 1;
-        const int np = __shfl(parts, src, kWave), nr = __shfl(rounds, src, kWave);
-        const int b = __shfl(base, src, kWave);
-        const int32_t gs = __shfl((int32_t)g, src, kWave);
-        for (int q = lane_id(); q < np * nr; q += kWave)
-            sp.work[b + q] = WorkItem{gs, q % np, np, q / np};
-    }
+    WorkItem *const out = sp.work + base;
+    for (int k = 0; k < rounds; ++k)
+        for (int q = 0; q < parts; ++q) out[k * parts + q] = WorkItem{(int32_t)g, q, parts, k};
 }
 
 __global__ void k_order_identity(int64_t G, int32_t *__restrict__ order,
