@@ -138,6 +138,7 @@ struct p3t_ctx {
     p3t::DevBuf step_off, step_idx;    // neighbour CSR of p3t_step
     p3t::DevBuf step_off2, step_idx2;  // ... merged with the special particles' pairs
     p3t::DevBuf kinds_cnt;
+    p3t::DevBuf direct_rows;           // partial sums of the direct sums
 };
 
 namespace p3t {
