@@ -637,20 +637,50 @@ int launch_force(p3t_ctx *ctx, double *acc, double *pot) {
 // ---------------------------------------------------------------------------
 // Leapfrog: v += dt_kick * a; x += dt_drift * v
 // ---------------------------------------------------------------------------
+// Bound by memory.  DRIFT false (dt_drift = 0): the positions stay where they
+// are and are not read; a velocity that is not finite still makes its position
+// NaN, as x += 0 v does.  VEC: two elements per thread and 16-byte accesses, for
+// arrays aligned to them.  (2^20 particles: drift 19.6 us, kick alone 19.5 ->
+// 13.1.)
+template <bool DRIFT, bool VEC>
 __global__ void k_kick_drift(int64_t n3, double *__restrict__ pos, double *__restrict__ vel,
                              const double *__restrict__ acc, double dk, double dd) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n3) return;
-    const double v = vel[k] + dk * acc[k];
-    vel[k] = v;
-    pos[k] = pos[k] + dd * v;
+    constexpr int W = VEC ? 2 : 1;
+    const int64_t k0 = W * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+    if (k0 >= n3) return;
+    if (VEC && k0 + 1 < n3) {
+        double2 v = *reinterpret_cast<const double2 *>(vel + k0);
+        const double2 a = *reinterpret_cast<const double2 *>(acc + k0);
+        v.x = v.x + dk * a.x;
+        v.y = v.y + dk * a.y;
+        *reinterpret_cast<double2 *>(vel + k0) = v;
+        if (DRIFT) {
+            double2 x = *reinterpret_cast<const double2 *>(pos + k0);
+            x.x = x.x + dd * v.x;
+            x.y = x.y + dd * v.y;
+            *reinterpret_cast<double2 *>(pos + k0) = x;
+        } else {
+            if (!isfinite(v.x)) pos[k0] = NAN;
+            if (!isfinite(v.y)) pos[k0 + 1] = NAN;
+        }
+        return;
+    }
+    const double v = vel[k0] + dk * acc[k0];
+    vel[k0] = v;
+    if (DRIFT) pos[k0] = pos[k0] + dd * v;
+    else if (!isfinite(v)) pos[k0] = NAN;
 }
 
 int launch_kick_drift(p3t_ctx *ctx, int64_t n, double *pos, double *vel, const double *acc,
                       double dt_kick, double dt_drift) {
     if (n <= 0) return P3T_OK;
-    k_kick_drift<<<blocks_for(3 * n, 256), 256, 0, ctx->stream>>>(3 * n, pos, vel, acc, dt_kick,
-                                                                   dt_drift);
+    const uintptr_t at = reinterpret_cast<uintptr_t>(pos) | reinterpret_cast<uintptr_t>(vel) |
+                         reinterpret_cast<uintptr_t>(acc);
+    const bool vec = at % 16 == 0;
+    auto kernel = dt_drift != 0.0 ? (vec ? k_kick_drift<true, true> : k_kick_drift<true, false>)
+                                  : (vec ? k_kick_drift<false, true> : k_kick_drift<false, false>);
+    kernel<<<blocks_for(3 * n, vec ? 512 : 256), 256, 0, ctx->stream>>>(3 * n, pos, vel, acc,
+                                                                       dt_kick, dt_drift);
     return check_hip(ctx, hipGetLastError(), "kick/drift");
 }
 
