@@ -163,6 +163,34 @@ struct RootCube {
     int bad;
 };
 
+// the cube of the box v (lo xyz, hi xyz) and the invalid-input flag v[6]
+__device__ __forceinline__ RootCube cube_of_box(const double v[kBboxRec], RootInfo *__restrict__ root,
+                                                int64_t *__restrict__ bad_rb) {
+    RootCube c;
+    double ext = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        c.lo[a] = v[a];
+        const double e = v[3 + a] - v[a];
+        if (e > ext) ext = e;
+    }
+    c.L = 1.0;
+    if (ext > 0.0) {
+        int e;
+        const double f = frexp(ext, &e);
+        c.L = (f == 0.5) ? ldexp(1.0, e - 1) : ldexp(1.0, e);
+    }
+    c.scale = ldexp(1.0, kMaxLevel) / c.L;
+    c.bad = v[6] != 0.0 ? 1 : 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        for (int a = 0; a < 3; ++a) root->lo[a] = c.lo[a];
+        root->L = c.L;
+        root->scale = c.scale;
+        root->bad_input = c.bad;
+        *bad_rb = c.bad;
+    }
+    return c;
+}
+
 __device__ __forceinline__ RootCube root_cube(const double *__restrict__ partial, int nbb,
                                               RootInfo *__restrict__ root,
                                               int64_t *__restrict__ bad_rb) {
@@ -190,29 +218,19 @@ __device__ __forceinline__ RootCube root_cube(const double *__restrict__ partial
         }
         v[6] = fmax(v[6], s7[k][6]);
     }
-    RootCube c;
-    double ext = 0.0;
+    return cube_of_box(v, root, bad_rb);
+}
+
+__device__ __forceinline__ uint64_t morton_key(const PosMass &r, const double lo[3], double scale) {
+    const double x[3] = {r.x, r.y, r.z};
+    uint64_t q[3];
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
-        c.lo[a] = v[a];
-        const double e = v[3 + a] - v[a];
-        if (e > ext) ext = e;
+        const double t = floor((x[a] - lo[a]) * scale);
+        const uint64_t v = (uint64_t)t;
+        q[a] = v > 0x1fffffull ? 0x1fffffull : v;
     }
-    c.L = 1.0;
-    if (ext > 0.0) {
-        int e;
-        const double f = frexp(ext, &e);
-        c.L = (f == 0.5) ? ldexp(1.0, e - 1) : ldexp(1.0, e);
-    }
-    c.scale = ldexp(1.0, kMaxLevel) / c.L;
-    c.bad = v[6] != 0.0 ? 1 : 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        for (int a = 0; a < 3; ++a) root->lo[a] = c.lo[a];
-        root->L = c.L;
-        root->scale = c.scale;
-        root->bad_input = c.bad;
-        *bad_rb = c.bad;
-    }
-    return c;
+    return (spread_bits3(q[0]) << 2) | (spread_bits3(q[1]) << 1) | spread_bits3(q[2]);
 }
 
 __global__ __launch_bounds__(kRsThreads) void k_keys_hist(const double *__restrict__ pos,
@@ -241,15 +259,7 @@ __global__ __launch_bounds__(kRsThreads) void k_keys_hist(const double *__restri
     for (int k = 0; k < kRsRounds; ++k) {
         const int64_t i = base + k * kRsThreads + threadIdx.x;
         if (i >= n) break;
-        const double x[3] = {r[k].x, r[k].y, r[k].z};
-        uint64_t q[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const double t = floor((x[a] - lo[a]) * scale);
-            const uint64_t v = (uint64_t)t;
-            q[a] = v > 0x1fffffull ? 0x1fffffull : v;
-        }
-        const uint64_t key = (spread_bits3(q[0]) << 2) | (spread_bits3(q[1]) << 1) | spread_bits3(q[2]);
+        const uint64_t key = morton_key(r[k], lo, scale);
         keys[i] = key;
         idx[i] = (int32_t)i;
         xm_in[i] = r[k];
@@ -386,6 +396,146 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
     if (LAST && blockIdx.x == 0 && tid == 0) so.gflag[n] = 0;
 }
 
+// ---------------------------------------------------------------------------
+// Few particles: a radix pass is three launches of a few microseconds each, so
+// up to kRankMax particles one launch does it all.  Every block reduces the
+// bounding box of all particles and holds all keys in LDS; it ranks kWave
+// particles of its own, one per lane, each wavefront counting the smaller keys
+// (and equal ones of lower index) in its share of the keys, and writes their
+// sorted entries.  A wavefront counts n / 16 keys; with the launches' gaps the
+// radix passes took 110 us at 1000 particles (14 us here) and 140 at 4096 (23).
+// ---------------------------------------------------------------------------
+constexpr int kRankThreads = 1024;
+constexpr int kRankPer = 8;                              // particles per thread
+constexpr int kRankMax = kRankThreads * kRankPer;
+constexpr int kRankWaves = kRankThreads / kWave;
+
+__global__ __launch_bounds__(kRankThreads) void k_rank_sort(
+    const double *__restrict__ pos, const double *__restrict__ mass, int n,
+    RootInfo *__restrict__ root, int64_t *__restrict__ bad_rb, uint64_t *__restrict__ keys,
+    int32_t *__restrict__ vals, PosMass *__restrict__ xm, int32_t *__restrict__ gflag) {
+    __shared__ uint64_t s_key[kRankMax];
+    __shared__ double s_box[kRankWaves][kBboxRec];
+    __shared__ int32_t s_cnt[kRankWaves][kWave];
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+    PosMass r[kRankPer];
+    double v[kBboxRec] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0};
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k) {
+        const int i = k * kRankThreads + tid;
+        if (i < n) r[k] = PosMass{pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], mass[i]};
+    }
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k) {
+        if (k * kRankThreads + tid >= n) continue;
+        const double x[3] = {r[k].x, r[k].y, r[k].z};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if (!isfinite(x[a])) v[6] = 1.0;
+            v[a] = fmin(v[a], x[a]);
+            v[3 + a] = fmax(v[3 + a], x[a]);
+        }
+        if (!(isfinite(r[k].m) && r[k].m > 0.0)) v[6] = 1.0;
+    }
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+        for (int a = 0; a < 3; ++a) {
+            v[a] = fmin(v[a], __shfl_xor(v[a], d, kWave));
+            v[3 + a] = fmax(v[3 + a], __shfl_xor(v[3 + a], d, kWave));
+        }
+        v[6] = fmax(v[6], __shfl_xor(v[6], d, kWave));
+    }
+    if (lane == 0)
+        for (int a = 0; a < kBboxRec; ++a) s_box[w][a] = v[a];
+    __syncthreads();
+    for (int k = 0; k < kRankWaves; ++k) {
+        for (int a = 0; a < 3; ++a) {
+            v[a] = fmin(v[a], s_box[k][a]);
+            v[3 + a] = fmax(v[3 + a], s_box[k][3 + a]);
+        }
+        v[6] = fmax(v[6], s_box[k][6]);
+    }
+    const RootCube cube = cube_of_box(v, root, bad_rb);
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k) {
+        const int i = k * kRankThreads + tid;
+        if (i < n) s_key[i] = morton_key(r[k], cube.lo, cube.scale);
+    }
+    __syncthreads();
+    // lane's particle against the wavefront's share [b, e) of the keys: those
+    // before the block's particles count when equal, those after do not
+    const int i0 = blockIdx.x * kWave, i = i0 + lane;
+    const uint64_t key = i < n ? s_key[i] : 0ull;
+    const int per = (n + kRankWaves - 1) / kRankWaves;
+    const int b = min(n, w * per), e = min(n, b + per);
+    const int e0 = min(e, max(b, i0)), e1 = min(e, max(b, i0 + kWave));
+    int cnt = 0;
+#pragma unroll 8
+    for (int j = b; j < e0; ++j) cnt += s_key[j] <= key;
+    for (int j = e0; j < e1; ++j) cnt += (s_key[j] < key) | ((s_key[j] == key) & (j < i));
+#pragma unroll 8
+    for (int j = e1; j < e; ++j) cnt += s_key[j] < key;
+    s_cnt[w][lane] = cnt;
+    __syncthreads();
+    if (w != 0 || i >= n) return;
+    int rank = 0;
+    for (int k = 0; k < kRankWaves; ++k) rank += s_cnt[k][lane];
+    keys[rank] = key;
+    vals[rank] = i;
+    xm[rank] = PosMass{pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], mass[i]};
+    gflag[rank] = 0;
+    if (i == 0) gflag[n] = 0;
+}
+
+// Up to kRankKeysMax particles: the same ranking from keys in memory (after the
+// bounding box and the keys), each wavefront bringing its share of them
+// through LDS 64 at a time.  The work grows with n^2: 15001 particles 25 us
+// against 131 of the radix passes.
+constexpr int kRankKeysMax = 24576;
+
+__global__ __launch_bounds__(kRankThreads) void k_rank_keys(
+    const uint64_t *__restrict__ kin, const PosMass *__restrict__ xm_in, int n,
+    uint64_t *__restrict__ keys, int32_t *__restrict__ vals, PosMass *__restrict__ xm,
+    int32_t *__restrict__ gflag) {
+    __shared__ uint64_t s_key[kRankWaves][kWave];
+    __shared__ int32_t s_cnt[kRankWaves][kWave];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int i0 = blockIdx.x * kWave, i = i0 + lane;
+    const uint64_t key = i < n ? kin[i] : 0ull;
+    // shares in whole runs of 64 keys, so that a run lies on one side of the
+    // block's own 64 particles or is theirs
+    const int runs = (n + kWave - 1) / kWave, per = (runs + kRankWaves - 1) / kRankWaves;
+    const int r1 = min(runs, (w + 1) * per);
+    int cnt = 0;
+    uint64_t pre = w * per * kWave + lane < n ? kin[w * per * kWave + lane] : ~0ull;
+    for (int r = w * per; r < r1; ++r) {
+        s_key[w][lane] = pre;   // (keys have 63 bits: padding counts as larger)
+        __builtin_amdgcn_wave_barrier();
+        const int nx = (r + 1) * kWave + lane;
+        pre = r + 1 < r1 && nx < n ? kin[nx] : ~0ull;
+        if (r < (int)blockIdx.x) {
+#pragma unroll 16
+            for (int j = 0; j < kWave; ++j) cnt += s_key[w][j] <= key;
+        } else if (r > (int)blockIdx.x) {
+#pragma unroll 16
+            for (int j = 0; j < kWave; ++j) cnt += s_key[w][j] < key;
+        } else {
+            for (int j = 0; j < kWave; ++j) cnt += (s_key[w][j] < key) | ((s_key[w][j] == key) & (j < lane));
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    s_cnt[w][lane] = cnt;
+    __syncthreads();
+    if (w != 0 || i >= n) return;
+    int rank = 0;
+    for (int k = 0; k < kRankWaves; ++k) rank += s_cnt[k][lane];
+    keys[rank] = key;
+    vals[rank] = i;
+    xm[rank] = xm_in[i];
+    gflag[rank] = 0;
+    if (i == 0) gflag[n] = 0;
+}
+
 // The moments folds count the groups per particle tile for the group scan when
 // the particles fit kScan2MaxTiles tiles (n + 1 flags).
 static bool group_tiles_counted(const p3t_ctx *ctx, int64_t n) {
@@ -401,6 +551,17 @@ int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n)
         kBboxMaxBlocks, (n + (int64_t)kRedThreads * kBboxUnroll - 1) / ((int64_t)kRedThreads * kBboxUnroll));
     const int nb = (int)((n + kRsTile - 1) / kRsTile);
     if ((rc = ensure(ctx, ctx->root, sizeof(RootInfo)))) return rc;
+    if ((rc = ensure(ctx, ctx->xm, n * sizeof(PosMass)))) return rc;
+    if ((rc = ensure(ctx, ctx->gflag, (n + 1) * sizeof(int32_t)))) return rc;
+    if (n <= kRankMax) {
+        if ((rc = ensure(ctx, ctx->keys[0], n * sizeof(uint64_t)))) return rc;
+        if ((rc = ensure(ctx, ctx->vals[0], n * sizeof(int32_t)))) return rc;
+        k_rank_sort<<<blocks_for(n, kWave), kRankThreads, 0, ctx->stream>>>(
+            pos, mass, (int)n, ptr<RootInfo>(ctx->root), ctx->hpin + kRbTopoBad,
+            ptr<uint64_t>(ctx->keys[0]), ptr<int32_t>(ctx->vals[0]), ptr<PosMass>(ctx->xm),
+            ptr<int32_t>(ctx->gflag));
+        return check_hip(ctx, hipGetLastError(), "rank sort");
+    }
     if ((rc = ensure(ctx, ctx->bbox, kBboxRec * nbb * sizeof(double)))) return rc;
     for (p3t::DevBuf *b : {&ctx->keys[0], &ctx->keys[1]})
         if ((rc = ensure(ctx, *b, n * sizeof(uint64_t)))) return rc;
@@ -409,9 +570,7 @@ int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n)
     if ((rc = ensure(ctx, ctx->hist, (size_t)kRsBins * nb * sizeof(int32_t)))) return rc;
     if ((rc = ensure(ctx, ctx->histc, (size_t)kRsBins * nb * sizeof(int32_t)))) return rc;
     if ((rc = ensure(ctx, ctx->rs_tot, kRsBins * sizeof(int32_t)))) return rc;
-    if ((rc = ensure(ctx, ctx->xm, n * sizeof(PosMass)))) return rc;
     if ((rc = ensure(ctx, ctx->xm_in, n * sizeof(PosMass)))) return rc;
-    if ((rc = ensure(ctx, ctx->gflag, (n + 1) * sizeof(int32_t)))) return rc;
     double *partial = ptr<double>(ctx->bbox);
     k_bbox<<<nbb, kRedThreads, 0, ctx->stream>>>(pos, mass, n, partial);
     int32_t *cnt = ptr<int32_t>(ctx->histc), *off = ptr<int32_t>(ctx->hist);
@@ -425,6 +584,15 @@ int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n)
                                                      ptr<int32_t>(ctx->vals[0]),
                                                      ptr<PosMass>(ctx->xm_in), cnt, nb);
     if ((rc = check_hip(ctx, hipGetLastError(), "root/keys"))) return rc;
+    if (n <= kRankKeysMax) {
+        k_rank_keys<<<blocks_for(n, kWave), kRankThreads, 0, ctx->stream>>>(
+            ptr<uint64_t>(ctx->keys[0]), ptr<PosMass>(ctx->xm_in), (int)n,
+            ptr<uint64_t>(ctx->keys[1]), ptr<int32_t>(ctx->vals[1]), ptr<PosMass>(ctx->xm),
+            ptr<int32_t>(ctx->gflag));
+        std::swap(ctx->keys[0], ctx->keys[1]);
+        std::swap(ctx->vals[0], ctx->vals[1]);
+        return check_hip(ctx, hipGetLastError(), "rank keys");
+    }
     const SortedOut so{ptr<PosMass>(ctx->xm_in), ptr<PosMass>(ctx->xm), ptr<int32_t>(ctx->gflag)};
     int src = 0;
     for (int pass = 0; pass < kRsPasses; ++pass) {
@@ -835,93 +1003,26 @@ __device__ __forceinline__ void leaf_moments(const MomentArrays &A, int64_t id) 
     store_node(A, A.root->L, id, A.level[id], 0, -1, f, cnt, M, Sx, Sy, Sz, lo, hi, q);
 }
 
-// Internal nodes are folded from their children staged in LDS in chunks of
-// kMomChunk children (see fold_chunk).
+// Internal nodes are folded from their children staged in LDS, kMomChunk
+// children at a time (see fold_chunk).
 constexpr int kMomChunk = 256;
 constexpr int kMomChildMax = 8;
-constexpr int kMomStage = kMomChunk + kMomChildMax - 1;
-constexpr int kMomThreads = 320;   // >= kMomStage: one staging round
-static_assert(kMomThreads >= kMomStage, "one staging round");
+constexpr int kMomStage = kMomChunk + kMomChildMax;
+constexpr int kMomThreads = 512;
+constexpr int kMomLanes = 8;       // lanes per parent
+constexpr int kMomFlagWaves = (kMomStage + kWave - 1) / kWave;
+static_assert(kMomThreads >= kMomFlagWaves * kWave, "one staging round");
 
-// What a parent's fold reads of each child, staged in LDS.
-struct ChildRec {
-    double M, Sx, Sy, Sz, cx, cy, cz;
-    double q[6];
-    double lo[3], hi[3];
-    int32_t count, first, n_child, pad;
+// what a parent's fold reads of each child: M, S (3), lo (3), hi (3), com (3), q (6)
+enum { kChM = 0, kChS = 1, kChLo = 4, kChHi = 7, kChCom = 10, kChQ = 13, kChDoubles = 19 };
+
+static_assert(sizeof(NodeWalk) == 12 * 8 && sizeof(NodeMP) == 10 * 8, "records of doubles");
+struct MomStage {
+    double d[kChDoubles][kMomStage];
+    int32_t count[kMomStage], first[kMomStage], n_child[kMomStage];
+    uint64_t starts[kMomFlagWaves + 1];        // children that start a parent (or end the level)
+    int32_t par[kMomChunk], at[kMomChunk], nc[kMomChunk];   // the chunk's parents
 };
-
-__device__ __forceinline__ ChildRec load_child(const MomentArrays &A, int64_t k) {
-    const NodeMP m = A.mp[k];
-    const NodeWalk &w = A.nw[k];
-    ChildRec r;
-    r.M = m.M;
-    r.Sx = A.S[k];
-    r.Sy = A.S[A.n_nodes + k];
-    r.Sz = A.S[2 * A.n_nodes + k];
-    r.cx = m.cx; r.cy = m.cy; r.cz = m.cz;
-    for (int a = 0; a < 6; ++a) r.q[a] = m.q[a];
-    for (int a = 0; a < 3; ++a) {
-        r.lo[a] = w.lo[a];
-        r.hi[a] = w.hi[a];
-    }
-    r.count = w.count;
-    r.first = w.first;
-    r.n_child = w.n_child;
-    r.pad = 0;
-    return r;
-}
-
-// fold of an internal node's nc (at most 8) children child(0 .. nc-1) in octant
-// order, the children's quadrupoles shifted to the node's centre of mass; the
-// node's count is the sum of its children's
-template <class Child>
-__device__ __forceinline__ void internal_moments(const MomentArrays &A, double L, int64_t id, int lev,
-                                                 int32_t first_child, const Child &child, int nc,
-                                                 TileCount &tc) {
-    double M = 0.0, Sx = 0.0, Sy = 0.0, Sz = 0.0;
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    double q[6] = {0, 0, 0, 0, 0, 0};
-    int32_t cnt = 0;
-    for (int k = 0; k < nc; ++k) {
-        const ChildRec c = child(k);
-        cnt += c.count;
-        M = M + c.M;
-        Sx = Sx + c.Sx;
-        Sy = Sy + c.Sy;
-        Sz = Sz + c.Sz;
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = fmin(lo[a], c.lo[a]);
-            hi[a] = fmax(hi[a], c.hi[a]);
-        }
-    }
-    const double cx = Sx / M, cy = Sy / M, cz = Sz / M;
-    for (int k = 0; k < nc; ++k) {
-        const ChildRec c = child(k);
-        const double dx = c.cx - cx, dy = c.cy - cy, dz = c.cz - cz;
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        const double Mk = c.M;
-        q[0] += c.q[0] + Mk * (3.0 * dx * dx - r2);
-        q[1] += c.q[1] + Mk * (3.0 * dy * dy - r2);
-        q[2] += c.q[2] + Mk * (3.0 * dz * dz - r2);
-        q[3] += c.q[3] + Mk * 3.0 * dx * dy;
-        q[4] += c.q[4] + Mk * 3.0 * dx * dz;
-        q[5] += c.q[5] + Mk * 3.0 * dy * dz;
-    }
-    A.count[id] = cnt;
-    const int32_t f = child(0).first;   // the node's first particle is its first child's
-    store_node(A, L, id, lev, nc, first_child, f, cnt, M, Sx, Sy, Sz, lo, hi, q);
-    // groups among the children (this node has more than n_crit members), or
-    // the root itself
-    if (cnt > A.n_crit) {
-        for (int k = 0; k < nc; ++k) {
-            const ChildRec c = child(k);
-            if (c.count <= A.n_crit || c.n_child == 0) mark_group(A, first_child + k, c.first, tc);
-        }
-    } else if (lev == 0) {
-        mark_group(A, (int32_t)id, f, tc);
-    }
-}
 
 // every leaf's moments; every internal node's child count and its children's
 // parent links (the topology's last step)
@@ -945,44 +1046,128 @@ __global__ __launch_bounds__(128) void k_moments_leaves(MomentArrays A, int32_t 
 }
 
 // The internal nodes of level lev whose first child lies in the chunk of
-// children [k0, k0 + kMomChunk) of the children level [cb, ce): a thread per
-// child stages that child's record in LDS (consecutive threads, consecutive
-// records), with the kMomChildMax - 1 children past the chunk so that every
-// parent whose first child is in the chunk has all its children on chip; the
-// thread of each parent's first child folds the parent.
-
-struct MomStage {
-    ChildRec c[kMomStage];
-    int32_t par[kMomStage];
-    int32_t before;   // parent of the child before the chunk (-1 at the level's start)
-};
-
+// children [k0, k0 + kMomChunk) of the children level [cb, ce).  A thread per
+// child stages that child's record in LDS, with the kMomChildMax children past
+// the chunk, so that every parent whose first child is in the chunk has all
+// its children on chip.  A launch is a chain of latencies, so a parent takes
+// eight lanes: each folds some components of M, S, lo, hi over the children in
+// octant order, then one of the quadrupole about the com, and stores some
+// elements of the node's records (us per level at 2^20 particles: one lane per
+// parent 9.7, sixteen 8.7, which read the children's com as often as there are
+// lanes, eight 7.0; top levels of 4096 particles: 52, 48, 38).
 __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, int lev, int64_t cb,
                                            int64_t ce, int64_t k0) {
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
     const double L = A.root->L;   // read while the stage fills
-    if (t < kMomStage) {
-        const int64_t k = k0 + t;
-        if (k < ce) {
-            st.c[t] = load_child(A, k);
-            st.par[t] = A.parent[k];
-        } else {
-            st.par[t] = -1;
+    const int64_t k = k0 + t;
+    const bool valid = t < kMomStage && k < ce;
+    bool start = k >= ce;
+    int32_t par = -1;
+    if (valid) {
+        const int32_t before = k > cb ? A.parent[k - 1] : -1;
+        par = A.parent[k];
+        const NodeMP m = A.mp[k];
+        const NodeWalk &nd = A.nw[k];
+        for (int a = 0; a < 3; ++a) {
+            st.d[kChLo + a][t] = nd.lo[a];
+            st.d[kChHi + a][t] = nd.hi[a];
+            st.d[kChS + a][t] = A.S[a * A.n_nodes + k];
         }
+        st.count[t] = nd.count;
+        st.first[t] = nd.first;
+        st.n_child[t] = nd.n_child;
+        st.d[kChM][t] = m.M;
+        st.d[kChCom][t] = m.cx;
+        st.d[kChCom + 1][t] = m.cy;
+        st.d[kChCom + 2][t] = m.cz;
+        for (int a = 0; a < 6; ++a) st.d[kChQ + a][t] = m.q[a];
+        start = before != par;   // a parent's children are consecutive
     }
-    if (t == kMomStage) st.before = k0 > cb ? A.parent[k0 - 1] : -1;
+    const uint64_t flags = ballot(start);
+    if (lane == 0 && w < kMomFlagWaves) st.starts[w] = flags;
+    if (t == 0) st.starts[kMomFlagWaves] = ~0ull;
+    __syncthreads();
+    int np = 0, rank = 0;
+    for (int v = 0; v < kMomChunk / kWave; ++v) {
+        uint64_t f = st.starts[v];
+        // starts past the level's end are not parents
+        const int64_t left = ce - (k0 + v * kWave);
+        f &= left >= kWave ? ~0ull : left > 0 ? (1ull << left) - 1 : 0ull;
+        if (v < w) rank += __popcll(f);
+        np += __popcll(f);
+    }
+    if (t < kMomChunk && valid && start) {
+        rank += count_below(flags);
+        const uint64_t next = lane == kWave - 1 ? st.starts[w + 1]
+                                                : (flags >> (lane + 1)) | (st.starts[w + 1] << (kWave - 1 - lane));
+        st.par[rank] = par;
+        st.at[rank] = t;
+        st.nc[rank] = __builtin_ctzll(next) + 1;
+    }
     __syncthreads();
     TileCount tc;
-    if (t < kMomChunk && k0 + t < ce) {
-        const int32_t p = st.par[t];
-        // a parent's children are consecutive
-        const int32_t before = t > 0 ? st.par[t - 1] : st.before;
-        if (before != p) {
-            int nc = 1;
-            while (nc < kMomChildMax && st.par[t + nc] == p) ++nc;
-            const ChildRec *c = st.c + t;
-            internal_moments(A, L, p, lev, (int32_t)(k0 + t), [c](int j) { return c[j]; }, nc,
-                             tc);
+    const int c = t % kMomLanes, row = lane & ~(kMomLanes - 1);
+    for (int p0 = 0; p0 < np; p0 += kMomThreads / kMomLanes) {
+        const int p = p0 + t / kMomLanes;
+        const bool mine = p < np;   // the same for a parent's lanes
+        const int at = mine ? st.at[p] : 0, nc = mine ? st.nc[p] : 0;
+        const int32_t id = mine ? st.par[p] : 0;
+        // lanes 0 - 3: sums of M, S; lanes 4 - 6: lo and hi of an axis; all:
+        // the member count (entries past the children are read, not used)
+        double acc = c < 4 ? 0.0 : INFINITY, hi = -INFINITY;
+        int32_t cnt = 0;
+        const double *src = st.d[c < 7 ? c : 0] + at, *his = st.d[c >= 4 && c < 7 ? c + 3 : kChHi] + at;
+#pragma unroll
+        for (int j = 0; j < kMomChildMax; ++j) {
+            const double v = src[j];
+            const double next = c < 4 ? acc + v : fmin(acc, v), top = fmax(hi, his[j]);
+            acc = j < nc ? next : acc;
+            hi = j < nc ? top : hi;
+            cnt += j < nc ? st.count[at + j] : 0;
+        }
+        const double M = __shfl(acc, row, kWave), Sx = __shfl(acc, row + 1, kWave),
+                     Sy = __shfl(acc, row + 2, kWave), Sz = __shfl(acc, row + 3, kWave);
+        const double cx = Sx / M, cy = Sy / M, cz = Sz / M;
+        // quadrupole component a: xx yy zz xy xz yz
+        const int a = c < 6 ? c : 0;
+        const bool diag = a < 3;
+        double q = 0.0;
+        const double *qs = st.d[kChQ + a] + at;
+#pragma unroll
+        for (int j = 0; j < kMomChildMax; ++j) {
+            const double dx = st.d[kChCom][at + j] - cx, dy = st.d[kChCom + 1][at + j] - cy,
+                         dz = st.d[kChCom + 2][at + j] - cz;
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            const double Mk = st.d[kChM][at + j];
+            const double u = a == 0 || a == 3 || a == 4 ? dx : a == 1 || a == 5 ? dy : dz;
+            const double v = a == 3 ? dy : dz;
+            const double on = Mk * (3.0 * u * u - r2), off = Mk * 3.0 * u * v;
+            const double next = q + (qs[j] + (diag ? on : off));
+            q = j < nc ? next : q;
+        }
+        if (!mine) continue;
+        const double side = ldexp(L, -lev);
+        const int32_t f = st.first[at];   // the node's first particle is its first child's
+        const int32_t child_first = (int32_t)(k0 + at);
+        auto pair = [](int32_t lo, int32_t hi) {
+            return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+        };
+        const double com = c == 0 ? cx : c == 1 ? cy : cz;
+        if (c >= 1 && c < 4) A.S[(c - 1) * A.n_nodes + id] = acc;
+        double *const nw = reinterpret_cast<double *>(A.nw + id);
+        double *const mp = reinterpret_cast<double *>(A.mp + id);
+        nw[c < 7 ? c : 10] = c < 3 ? com : c == 3 ? side * side : c < 7 ? acc : pair(child_first, nc);
+        if (c >= 4) nw[c < 7 ? c + 3 : 11] = c < 7 ? hi : pair(f, cnt);
+        if (c < 4) mp[c] = c < 3 ? com : M;
+        if (c < 6) mp[4 + c] = q;
+        if (c == 7) A.count[id] = cnt;
+        // groups among the children (this node has more than n_crit members), or
+        // the root itself
+        if (cnt > A.n_crit) {
+            if (c < nc && (st.count[at + c] <= A.n_crit || st.n_child[at + c] == 0))
+                mark_group(A, child_first + c, st.first[at + c], tc);
+        } else if (lev == 0 && c == 0) {
+            mark_group(A, id, f, tc);
         }
     }
     flush_tile_counts(A, tc);
@@ -996,10 +1181,12 @@ __global__ __launch_bounds__(kMomThreads) void k_moments_level(MomentArrays A, i
     fold_chunk(A, st, lev, cb, ce, cb + (int64_t)blockIdx.x * kMomChunk);
 }
 
-// The top levels top .. 0 (children levels of at most kMomTopChildren nodes)
-// in one block, chunk after chunk; the block's barriers order each level after
-// the one below it (one compute unit: the block sees its own writes).
-constexpr int64_t kMomTopChildren = 4 * kMomChunk;
+// The top levels top .. 0 (children levels of at most kMomTopChildren nodes, one
+// chunk) in one block; the block's barriers order each level after the one
+// below it (one compute unit: the block sees its own writes).  A level of more
+// chunks is shorter as a launch of its own (6 us) than as chunks one after the
+// other (4.5 us each).
+constexpr int64_t kMomTopChildren = kMomChunk;
 __global__ __launch_bounds__(kMomThreads) void k_moments_top(MomentArrays A, int top,
                                                             LevelStarts ls) {
     __shared__ MomStage st;
@@ -1077,17 +1264,49 @@ __device__ __forceinline__ GroupInfo group_info(const NodeWalk &nd, int32_t id) 
     return g;
 }
 
-// the group record of a flagged particle, at its rank among the flags
-struct GroupSink {
-    const int32_t *node_at;
-    const NodeWalk *nw;
-    GroupInfo *grp;
-    __device__ __forceinline__ void operator()(int64_t a, int32_t slot, int32_t flag) const {
-        if (!flag) return;
-        const int32_t id = node_at[a];
-        grp[slot] = group_info(nw[id], id);
+// The records of a tile's groups: the flagged particles of the tile, collected
+// in LDS in order, and then a group per thread (the records' reads and writes
+// side by side: 5 us at any size, against 13 one after the other).
+// slot_n receives the number of groups.
+__global__ __launch_bounds__(kScan2Threads) void k_group_tiles(const int32_t *__restrict__ flag,
+                                                               int64_t n,
+                                                               const int32_t *__restrict__ gtile,
+                                                               int32_t *__restrict__ slot_n,
+                                                               const int32_t *__restrict__ node_at,
+                                                               const NodeWalk *__restrict__ nw,
+                                                               GroupInfo *__restrict__ grp) {
+    constexpr int kWaves = kScan2Threads / kWave;
+    __shared__ int32_t s_before[kWaves], s_wsum[kWaves], s_at[kScan2Tile];
+    const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
+    int32_t before = 0;
+    for (int64_t b = tid; b < blockIdx.x; b += kScan2Threads) before += gtile[b];
+    // the thread's consecutive flags
+    const int64_t base = (int64_t)blockIdx.x * kScan2Tile + (int64_t)tid * kScan2Items;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < kScan2Items; ++k)
+        if (base + k < n && flag[base + k]) mine |= 1u << k;
+    before = wave_sum(before);
+    const int cnt = __popc(mine);
+    const int incl = wave_incl_scan(cnt);
+    if (lane == 0) s_before[w] = before;
+    if (lane == kWave - 1) s_wsum[w] = incl;
+    __syncthreads();
+    int32_t start = 0, total = 0;
+    int at = incl - cnt;
+    for (int k = 0; k < kWaves; ++k) {
+        start += s_before[k];
+        total += s_wsum[k];
+        at += k < w ? s_wsum[k] : 0;
     }
-};
+    for (; mine; mine &= mine - 1) s_at[at++] = tid * kScan2Items + __builtin_ctz(mine);
+    __syncthreads();
+    for (int k = tid; k < total; k += kScan2Threads) {
+        const int32_t id = node_at[(int64_t)blockIdx.x * kScan2Tile + s_at[k]];
+        grp[start + k] = group_info(nw[id], id);
+    }
+    if (tid == 0 && blockIdx.x == gridDim.x - 1) *slot_n = start + total;
+}
 
 // (more than kScan2MaxTiles tiles of particles) also clears the walk's
 // statistics words (zero, nz of them)
@@ -1117,9 +1336,9 @@ int build_groups(p3t_ctx *ctx) {
     if (group_tiles_counted(ctx, n)) {
         // the folds counted the groups per tile; the scan places the group
         // records itself
-        k_scan2_tiles<int32_t><<<(unsigned)tiles, kScan2Threads, 0, ctx->stream>>>(
-            flag, n + 1, ptr<int32_t>(ctx->gtile), slot + n,
-            GroupSink{node_at, ptr<NodeWalk>(ctx->node_walk), ptr<GroupInfo>(ctx->grp)});
+        k_group_tiles<<<(unsigned)tiles, kScan2Threads, 0, ctx->stream>>>(
+            flag, n, ptr<int32_t>(ctx->gtile), slot + n, node_at, ptr<NodeWalk>(ctx->node_walk),
+            ptr<GroupInfo>(ctx->grp));
         return check_hip(ctx, hipGetLastError(), "groups");
     }
     if ((rc = scan_exclusive_i32(ctx, flag, slot, n + 1, nullptr))) return rc;

@@ -540,7 +540,8 @@ static int build_order(p3t_ctx *ctx, int64_t stride) {
 
 static int run_walk_stats(p3t_ctx *ctx, const int32_t *G_dev, int64_t stride, WalkStats *ws) {
     // few large blocks: the block results meet in same-address atomics
-    k_walk_stats<<<32, 1024, 0, ctx->stream>>>(
+    const int64_t fit = (ctx->n_nodes + 1023) / 1024;
+    k_walk_stats<<<(unsigned)(fit < 32 ? fit : 32), 1024, 0, ctx->stream>>>(
         ptr<GroupInfo>(ctx->grp), G_dev, ptr<int64_t>(ctx->cnt), stride,
         ptr<int32_t>(ctx->node_nchild), ctx->n_nodes, ctx->prm.precision == P3T_PREC_FP64, ws,
         ptr<int32_t>(ctx->grank));
