@@ -282,7 +282,7 @@ typedef struct {
  * particle's time is a multiple of the doubled step.  Each connected
  * component of the neighbour graph is integrated on its own: by a group of
  * lanes of a wavefront (fewer than 32 or 64 members), a workgroup (fewer than 1024)
- * or grid-wide launches per block step.
+ * or one grid-wide launch per block step.
  *   nsteps   device [n] int32 out (Hermite steps per particle) or NULL
  *   stats    host out or NULL
  * Synchronises the stream.  Errors: EINVAL, ENOMEM, ELIMIT, EHIP. */

@@ -124,8 +124,8 @@ struct p3t_ctx {
     // (the device holds how many there are), then one item per other group.
     int64_t n_split = 0, n_items = 0;
     p3t::DevBuf work, fpart;           // items and split groups; partial sums
-    p3t::DevBuf hard_ix, hard_state;   // hard part: components and integrator state
-    p3t::DevBuf hard_giant;            // ... and the step bookkeeping of the largest components
+    p3t::DevBuf hard_ix, hard_state;   // hard part: components, members and lists
+    p3t::DevBuf hard_giant;            // ... and the state of the largest components
     // the hard part's concurrent classes (aux_streams); the neighbour search
     // runs on aux[0] too, never at the same time (each host-synchronised)
     hipStream_t aux[4] = {nullptr, nullptr, nullptr, nullptr};
