@@ -117,7 +117,7 @@ struct p3t_ctx {
     p3t::DevBuf gflag, gscan, grp;
     p3t::DevBuf cnt, off, c_idx, p_idx, n_idx;
     p3t::DevBuf wstack, readback, scan_tmp, nbr_cnt, nbr_slots, nbr_scan;
-    p3t::DevBuf vjp_gx, vjp_gm, vjp_cell, bbox;
+    p3t::DevBuf vjp_part, vjp_cell, bbox;
     p3t::DevBuf seg_end, gorder, grank;
     // Work items of the interaction and adjoint kernels (walk.hip): the items
     // of the n_split first groups of the launch order in [0, n_items) of `work`
@@ -255,11 +255,11 @@ int launch_neighbors(p3t_ctx *ctx, int64_t *offsets, int32_t *idx, int64_t cap, 
                      hipEvent_t t0, hipEvent_t t1);
 
 // VJP (vjp.hip).  launch_vjp takes its workspaces from the context;
-// launch_vjp_ws from the caller: gx [3 n], gm [n] and cadj [10 n_nodes] doubles
-// (gx and gm are written before they are read, cadj is cleared first).
+// launch_vjp_ws from the caller: padj [n][4] and cadj [n_nodes][9] doubles (padj is
+// written before it is read, cadj is cleared first).
 int launch_vjp(p3t_ctx *ctx, const double *w, const double *c, double *gpos, double *gmass);
 int launch_vjp_ws(p3t_ctx *ctx, const double *w, const double *c, double *gpos, double *gmass,
-                  double *gx, double *gm, double *cadj);
+                  double *padj, double *cadj);
 
 // Hard part (hard.hip): force and jerk over neighbour lists; Hermite block-step
 // integration over one soft step.

@@ -205,7 +205,7 @@ extern "C" void p3t_destroy(p3t_ctx *ctx) {
                       &ctx->node_prefix, &ctx->node_S, &ctx->node_walk, &ctx->node_mp, &ctx->gflag,
                       &ctx->gscan, &ctx->grp, &ctx->cnt, &ctx->off, &ctx->c_idx, &ctx->p_idx,
                       &ctx->n_idx, &ctx->wstack, &ctx->readback, &ctx->scan_tmp,
-                      &ctx->nbr_cnt, &ctx->nbr_slots, &ctx->nbr_scan, &ctx->vjp_gx, &ctx->vjp_gm, &ctx->vjp_cell, &ctx->bbox,
+                      &ctx->nbr_cnt, &ctx->nbr_slots, &ctx->nbr_scan, &ctx->vjp_part, &ctx->vjp_cell, &ctx->bbox,
                       &ctx->seg_end, &ctx->gorder, &ctx->grank, &ctx->work, &ctx->fpart, &ctx->hard_ix,
                       &ctx->hard_state, &ctx->step_off, &ctx->step_idx, &ctx->step_off2,
                       &ctx->step_idx2, &ctx->kinds_cnt, &ctx->hard_giant, &ctx->direct_rows};
@@ -349,7 +349,8 @@ extern "C" int p3t_long_force_vjp_noalloc(p3t_ctx *ctx, const double *w, const d
                          "p3t_long_force_vjp_noalloc needs the build's lists; they were released");
     if (!w || !gpos || !gmass) return set_error(ctx, P3T_EINVAL, "bad VJP buffers");
     const int64_t n = ctx->n, nn = ctx->n_nodes;
-    // gx [3 n], gm [n], cell adjoints [10 n_nodes], each 256-byte aligned
+    // the particles' adjoints (room for 3 n and n, each 256-byte aligned) and the
+    // cells' (room for 10 n_nodes)
     const size_t a = 256 / sizeof(double);
     const size_t ngx = (3 * (size_t)n + a - 1) / a * a, ngm = ((size_t)n + a - 1) / a * a;
     const size_t need = (ngx + ngm + 10 * (size_t)nn) * sizeof(double);
@@ -360,9 +361,9 @@ extern "C" int p3t_long_force_vjp_noalloc(p3t_ctx *ctx, const double *w, const d
                          need, (long long)n, (long long)nn, kScratchBytes);
     int rc = check_hip(ctx, hipSetDevice(ctx->device), "set device");
     if (rc) return rc;
-    double *gx = static_cast<double *>(ctx->scratch), *gm = gx + ngx, *cadj = gm + ngm;
+    double *padj = static_cast<double *>(ctx->scratch), *cadj = padj + (ngx + ngm);
     if ((rc = mark(ctx, EV_VJP))) return rc;
-    if ((rc = launch_vjp_ws(ctx, w, c, gpos, gmass, gx, gm, cadj))) return rc;
+    if ((rc = launch_vjp_ws(ctx, w, c, gpos, gmass, padj, cadj))) return rc;
     if ((rc = mark(ctx, EV_VJP + 1))) return rc;
     ctx->ms_vjp = -1.0;
     return P3T_OK;

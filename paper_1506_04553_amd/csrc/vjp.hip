@@ -36,10 +36,16 @@
 // as in the interaction kernel; K and W themselves are evaluated in FP64) and
 // summed in FP64.  Scatter to list entries uses FP64 atomic adds, one per
 // (group, entry, component) after reduction over the group's members, so the
-// result is reproducible up to the order of those atomic additions.  The cell
-// adjoints are held component-major ([10][n_nodes]): the ten adds of one entry
-// then fall on ten different cache lines, where in cell-major order they
-// would queue on one line.  The push-down of the cell adjoints is FP64.
+// result is reproducible up to the order of those atomic additions.  With
+// several dies these adds are done at the memory side, at about 13.6 requests of
+// 64 bytes a nanosecond, and that rate bounds the second pass in mixed precision:
+// the components of an entry lie side by side (a particle's dx, dy, dz, dm; a
+// cell's dl/dr, dl/dM and dl/dQ, of which only five parts are needed), and a
+// wavefront hands its sums over through LDS so that neighbouring lanes add to
+// neighbouring words.  The second pass over 262144 particles (King W0 = 9, mixed):
+// 26.5 million requests and 2.31 ms, where component-major arrays and a lane's
+// own adds made 39.8 million and took 2.93; without any adds it takes 1.83.
+// The push-down of the cell adjoints is FP64.
 #include <math.h>
 
 #include "device_util.h"
@@ -262,8 +268,8 @@ __device__ __forceinline__ VjpCell<R> stage_cell(const NodeMP &c, const double s
 // Terms are summed in R over runs of at most kFold and each run's sum is added
 // to an FP64 accumulator.
 constexpr int kFold = 32;
-// a run of member terms is parked one lane per member and row, half a run at a time
-static_assert(kFold == 32, "two halves of 16 members");
+// a run of member terms is parked one lane per member and row, 16 members at a time
+static_assert(kFold % 16 == 0, "whole runs");
 
 // a list particle as staged in LDS: position (shifted) and mass
 template <class R>
@@ -311,7 +317,7 @@ template <class R>
 __global__ __launch_bounds__(kVjpThreads) void k_vjp_i(
     const GroupInfo *__restrict__ grp, ListsDev L, WorkDev wd, const PosMass *__restrict__ xm,
     const int32_t *__restrict__ perm, const double *__restrict__ wv, const double *__restrict__ cv,
-    VjpParams vp, double *__restrict__ gx, double *__restrict__ gm, int64_t n) {
+    VjpParams vp, double *__restrict__ padj) {
     __shared__ VjpPart<R> s_p[kVjpTile];
     __shared__ int32_t s_j[kVjpTile];
     __shared__ double s_red[3][kVjpThreads];
@@ -366,10 +372,8 @@ __global__ __launch_bounds__(kVjpThreads) void k_vjp_i(
             double r[3] = {0, 0, 0};
             for (int sidx = 0; sidx < nslice; ++sidx)
                 for (int a = 0; a < 3; ++a) r[a] += s_red[a][sidx * pad + li];
-            gx[i] = r[0];
-            gx[n + i] = r[1];
-            gx[2 * n + i] = r[2];
-            gm[i] = 0.0;
+            for (int a = 0; a < 3; ++a) padj[4 * (int64_t)i + a] = r[a];
+            padj[4 * (int64_t)i + 3] = 0.0;
         }
     }
 }
@@ -377,9 +381,40 @@ __global__ __launch_bounds__(kVjpThreads) void k_vjp_i(
 // ---------------------------------------------------------------------------
 // Pass 2: per list entry (particle j or cell c), the sum over the group's
 // members, scattered with one atomic add per component; the cell terms also
-// give the members their i-side cell terms.  Cell adjoints are
-// component-major: component a of cell c at cadj[a * n_nodes + c].
+// give the members their i-side cell terms.  The adjoints of particle j are at
+// padj + 4 j, those of cell c at cadj + cell_adj(quadrupole) c.
 // ---------------------------------------------------------------------------
+// dl/dr, dl/dM and, of dl/dQ = S, Sxx - Szz, Syy - Szz, Sxy, Sxz and Syz: the form
+// 3 S - tr(S) I, the only use of S, depends on no more
+__host__ __device__ constexpr int cell_adj(bool quad) { return quad ? 9 : 4; }
+
+// Adds the N words v of every lane with id >= 0 to dst + N id; `buf` is 16 N words
+// of LDS of the wavefront's own.
+template <int N>
+__device__ __forceinline__ void scatter_add(double *buf, const double v[N], int32_t id, int lane,
+                                            double *__restrict__ dst) {
+    auto in_order = [] {   // LDS accesses of one wavefront complete in program order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+#pragma unroll 1
+    for (int r = 0; r < kWave; r += 16) {
+        in_order();
+        if ((lane & 48) == r)
+            for (int a = 0; a < N; ++a) buf[(lane & 15) * N + a] = v[a];
+        in_order();
+#pragma unroll
+        for (int e0 = 0; e0 < 16 * N; e0 += kWave) {
+            const int e = e0 + lane;
+            const int32_t to = __shfl(id, r + min(e / N, 15), kWave);
+            if (e < 16 * N && to >= 0) {
+                const double x = buf[e];
+                if (x != 0.0) atomicAdd(&dst[(int64_t)to * N + e % N], x);
+            }
+        }
+    }
+}
+
 // a group member as staged in LDS: position (shifted), w and c
 template <class R>
 struct alignas(4 * sizeof(R)) VjpMember {
@@ -406,17 +441,50 @@ __device__ __forceinline__ void vjp_scatter_pp(const VjpMember<R> *si, const int
     }
 }
 
+// Members k0 .. min(k0 + 16, k1) - 1 one after the other: term(k, g) evaluates
+// what the lane's entry gives member k, and m ends with the sum over the lanes of
+// a row for one member per lane (row_member), taken four members at a time.
+__device__ __forceinline__ int row_member(int lane) {
+    return (lane & 12) + RowSums4::which(lane);
+}
+template <class R, class F>
+__device__ __forceinline__ void row_runs(int k0, int k1, int lane, R m[3], F term) {
+    const RowSums4 sums(lane);
+    const int left = k1 - k0;
+#pragma unroll 1
+    for (int u = 0; u < 16 && u < left; u += 4) {
+        R v[3], t[2][3] = {{0, 0, 0}, {0, 0, 0}};
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            if (u + 2 * c >= left) continue;
+            R g[3], gn[3] = {0, 0, 0};
+            term(k0 + u + 2 * c, g);
+            if (u + 2 * c + 1 < left) term(k0 + u + 2 * c + 1, gn);
+            for (int a = 0; a < 3; ++a) t[c][a] = sums.pair(g[a], gn[a]);
+        }
+        const bool mine = (lane & 12) == u;
+        for (int a = 0; a < 3; ++a) {
+            v[a] = sums.quad(t[0][a], t[1][a]);
+            m[a] = mine ? v[a] : m[a];
+        }
+    }
+}
+
+// (the bound on the blocks: 2.39 ms became 2.31 in the case above with four
+// wavefronts per SIMD; it spills where a cell's K is evaluated, and FP64 with
+// three takes 208 us instead of 197 for 15001 particles)
 template <class R, bool CELL_K, bool QUAD>
-__global__ __launch_bounds__(kVjpThreads) void k_vjp_scatter(
+__global__ __launch_bounds__(kVjpThreads, sizeof(R) == 4 && !CELL_K ? 4 : 2) void k_vjp_scatter(
     const GroupInfo *__restrict__ grp, ListsDev L, WorkDev wd, const PosMass *__restrict__ xm,
     const NodeMP *__restrict__ mp,
     const int32_t *__restrict__ perm, const double *__restrict__ wv, const double *__restrict__ cv,
-    VjpParams vp, double *__restrict__ gx, double *__restrict__ gm, double *__restrict__ cadj,
-    int64_t n, int64_t n_nodes) {
+    VjpParams vp, double *__restrict__ padj, double *__restrict__ cadj) {
     __shared__ VjpMember<R> s_i[kVjpThreads];
     __shared__ int32_t s_id[kVjpThreads];
     // per wavefront and member: the member's cell terms dl/dr (FP64 partials)
     __shared__ double s_gr[kVjpThreads / kWave][kVjpThreads][3];
+    constexpr int NC = cell_adj(QUAD);
+    __shared__ double s_out[kVjpThreads / kWave][16 * NC];
     const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
     VjpShare share;
     if (!vjp_share<R>(grp, wd, share)) return;
@@ -469,63 +537,45 @@ __global__ __launch_bounds__(kVjpThreads) void k_vjp_scatter(
             for (int k0 = 0; k0 < nc; k0 += kFold) {
                 const int k1 = min(nc, k0 + kFold);
                 R p[4] = {0, 0, 0, 0};
-                R mg[2][3] = {{0, 0, 0}, {0, 0, 0}};
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int kh = min(k1, k0 + 16 * (h + 1));
-                    for (int k = k0 + 16 * h; k < kh; ++k) {
+#pragma unroll 1
+                for (int r0 = k0; r0 < k1; r0 += 16) {
+                    R mg[3] = {0, 0, 0};
+                    row_runs(r0, k1, lane, mg, [&](int k, R gd[3]) {
                         const VjpMember<R> q = s_i[k];
-                        R gd[3], gmj;
+                        R gmj;
                         pair_grad<R, false>(xj - q.x, yj - q.y, zj - q.z, mj, q.wx, q.wy, q.wz, q.c,
                                             vp, gd, gmj);
                         p[0] += gd[0]; p[1] += gd[1]; p[2] += gd[2]; p[3] += gmj;
-                        const bool mine = (lane & 15) == ((k - k0) & 15);
-                        for (int a = 0; a < 3; ++a) {
-                            const R t = row_sum(gd[a]);
-                            mg[h][a] = mine ? t : mg[h][a];
-                        }
+                    });
+                    const int k = r0 + row_member(lane);
+                    for (int a = 0; a < 3; ++a) {
+                        mg[a] += __shfl_xor(mg[a], 16, kWave);
+                        mg[a] += __shfl_xor(mg[a], 32, kWave);
+                        if (lane < 16 && k < k1) s_gr[w][k][a] -= (double)mg[a];   // -dl/dd
                     }
                 }
                 for (int a = 0; a < 4; ++a) acc[a] += (double)p[a];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    for (int a = 0; a < 3; ++a) {
-                        R t = mg[h][a];
-                        t += __shfl_xor(t, 16, kWave);
-                        t += __shfl_xor(t, 32, kWave);
-                        mg[h][a] = t;
-                    }
-                    if (lane < 16 && k0 + 16 * h + lane < k1)   // the member's part: -dl/dd
-                        for (int a = 0; a < 3; ++a)
-                            s_gr[w][k0 + 16 * h + lane][a] -= (double)mg[h][a];
-                }
             }
-            if (valid) {
-                atomicAdd(&gx[j], acc[0]);
-                atomicAdd(&gx[n + j], acc[1]);
-                atomicAdd(&gx[2 * n + j], acc[2]);
-                atomicAdd(&gm[j], acc[3]);
-            }
+            scatter_add<4>(s_out[w], acc, valid ? j : -1, lane, padj);
         }
         // near particles (the list may hold a member): a lane per entry, this
         // side only
-        for (int64_t e = nf + tid; e < np; e += kVjpThreads) {
-            const int32_t j = n_idx[nb + (e - nf)];
-            const PosMass pj = xm[j];
-            const R xj = (R)(pj.x - sh[0]), yj = (R)(pj.y - sh[1]), zj = (R)(pj.z - sh[2]);
-            const R mj = (R)pj.m;
+        for (int64_t e0 = nf + (int64_t)w * kWave; e0 < np; e0 += kVjpThreads) {
+            const bool valid = e0 + lane < np;
+            int32_t j = -1;
             double acc[4] = {0, 0, 0, 0};
-            vjp_scatter_pp<R, true>(s_i, s_id, nc, j, xj, yj, zj, mj, vp, acc);
-            atomicAdd(&gx[j], acc[0]);
-            atomicAdd(&gx[n + j], acc[1]);
-            atomicAdd(&gx[2 * n + j], acc[2]);
-            atomicAdd(&gm[j], acc[3]);
+            if (valid) {
+                j = n_idx[nb + (e0 + lane - nf)];
+                const PosMass pj = xm[j];
+                const R xj = (R)(pj.x - sh[0]), yj = (R)(pj.y - sh[1]), zj = (R)(pj.z - sh[2]);
+                vjp_scatter_pp<R, true>(s_i, s_id, nc, j, xj, yj, zj, (R)pj.m, vp, acc);
+            }
+            scatter_add<4>(s_out[w], acc, j, lane, padj);
         }
         // cells: a lane per entry, the members from LDS.  Each pair's dl/dr
         // counts for both sides: the cell's sums stay in the lane; the
         // member's are summed over each row of 16 entries (a fixed tree) and
-        // parked in the row's lane (k - k0) mod 16 of mg[half] for the run of
-        // members k0 .. k1 - 1; after the run a butterfly over the four rows
+        // parked in one of the row's lanes for a run of 16 members; after the run a butterfly over the four rows
         // completes each member's sum, which joins the wavefront's FP64
         // partials in s_gr.  Lanes past the end hold a massless cell far away
         // and add zero.
@@ -543,13 +593,12 @@ __global__ __launch_bounds__(kVjpThreads) void k_vjp_scatter(
             for (int k0 = 0; k0 < nc; k0 += kFold) {
                 const int k1 = min(nc, k0 + kFold);
                 R p[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                R mg[2][3] = {{0, 0, 0}, {0, 0, 0}};
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int kh = min(k1, k0 + 16 * (h + 1));
-                    for (int k = k0 + 16 * h; k < kh; ++k) {
+#pragma unroll 1
+                for (int r0 = k0; r0 < k1; r0 += 16) {
+                    R mg[3] = {0, 0, 0};
+                    row_runs(r0, k1, lane, mg, [&](int k, R gr[3]) {
                         const VjpMember<R> q = s_i[k];
-                        R gr[3], gM, S[6];
+                        R gM, S[6];
                         if (CELL_K) {
                             CellGrad<R> cg;
                             cell_grad<R, true, QUAD>(q.x - c.x, q.y - c.y, q.z - c.z, c.M, c.q,
@@ -561,37 +610,26 @@ __global__ __launch_bounds__(kVjpThreads) void k_vjp_scatter(
                             cell_grad_far<R, QUAD>(q.x - c.x, q.y - c.y, q.z - c.z, c.M, c.q, q.wx,
                                                    q.wy, q.wz, q.c, (R)vp.eps2, gr, gM, S);
                         }
+                        // (a massless padding cell gives dl/dr = 0 exactly)
                         p[0] -= gr[0]; p[1] -= gr[1]; p[2] -= gr[2];
                         p[3] += gM;
                         if (QUAD)
                             for (int a = 0; a < 6; ++a) p[4 + a] += S[a];
-                        // (a massless padding cell gives dl/dr = 0 exactly)
-                        const bool mine = (lane & 15) == ((k - k0) & 15);
-                        for (int a = 0; a < 3; ++a) {
-                            const R t = row_sum(gr[a]);
-                            mg[h][a] = mine ? t : mg[h][a];
-                        }
+                    });
+                    // the four rows' parts of each member's sum
+                    const int k = r0 + row_member(lane);
+                    for (int a = 0; a < 3; ++a) {
+                        mg[a] += __shfl_xor(mg[a], 16, kWave);
+                        mg[a] += __shfl_xor(mg[a], 32, kWave);
+                        if (lane < 16 && k < k1) s_gr[w][k][a] += (double)mg[a];
                     }
                 }
                 for (int a = 0; a < 10; ++a) acc[a] += (double)p[a];
-                // the four rows' parts of each member's sum: lane j of row 0
-                // then holds member k0 + 16 h + j's
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    for (int a = 0; a < 3; ++a) {
-                        R t = mg[h][a];
-                        t += __shfl_xor(t, 16, kWave);
-                        t += __shfl_xor(t, 32, kWave);
-                        mg[h][a] = t;
-                    }
-                    if (lane < 16 && k0 + 16 * h + lane < k1)
-                        for (int a = 0; a < 3; ++a)
-                            s_gr[w][k0 + 16 * h + lane][a] += (double)mg[h][a];
-                }
             }
-            if (valid)
-                for (int a = 0; a < 10; ++a)
-                    if (acc[a] != 0.0) atomicAdd(&cadj[a * n_nodes + cid], acc[a]);
+            acc[4] -= acc[6];
+            acc[5] -= acc[6];
+            for (int a = 6; a < 9; ++a) acc[a] = acc[a + 1];
+            scatter_add<NC>(s_out[w], acc, valid ? cid : -1, lane, cadj);
         }
         __syncthreads();
         // the members' cell terms, wavefront partials in a fixed order (another
@@ -602,7 +640,7 @@ __global__ __launch_bounds__(kVjpThreads) void k_vjp_scatter(
             for (int a = 0; a < 3; ++a) {
                 double r = 0.0;
                 for (int v = 0; v < kVjpThreads / kWave; ++v) r += s_gr[v][tid][a];
-                atomicAdd(&gx[a * n + i], r);
+                atomicAdd(&padj[4 * (int64_t)i + a], r);
             }
         }
     }
@@ -618,17 +656,18 @@ struct Form {
     double g;
 };
 
-// adj: component a at adj[a * stride]
-__device__ __forceinline__ void form_add_own(Form &f, const double *adj, int64_t stride, double M) {
-    double v[10];
-    for (int a = 0; a < 10; ++a) v[a] = adj[a * stride];
-    const double tr = v[4] + v[5] + v[6];
-    f.B[0] += 3.0 * v[4] - tr;
-    f.B[1] += 3.0 * v[5] - tr;
-    f.B[2] += 3.0 * v[6] - tr;
-    f.B[3] += 3.0 * v[7];
-    f.B[4] += 3.0 * v[8];
-    f.B[5] += 3.0 * v[9];
+// adj: the cell's components, as many as `quad` has
+__device__ __forceinline__ void form_add_own(Form &f, const double *adj, bool quad, double M) {
+    double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    for (int a = 0; a < 4; ++a) v[a] = adj[a];
+    if (quad)
+        for (int a = 4; a < 9; ++a) v[a] = adj[a];
+    f.B[0] += 2.0 * v[4] - v[5];
+    f.B[1] += 2.0 * v[5] - v[4];
+    f.B[2] -= v[4] + v[5];
+    f.B[3] += 3.0 * v[6];
+    f.B[4] += 3.0 * v[7];
+    f.B[5] += 3.0 * v[8];
     f.b[0] += v[0] / M;
     f.b[1] += v[1] / M;
     f.b[2] += v[2] / M;
@@ -652,8 +691,8 @@ __device__ __forceinline__ void form_shift(Form &f, const double e[3]) {
 __global__ void k_vjp_down(int64_t n_nodes, const int32_t *__restrict__ nchild,
                            const int32_t *__restrict__ parent, const NodeMP *__restrict__ mp,
                            const NodeWalk *__restrict__ nw, const double *__restrict__ cadj,
-                           const PosMass *__restrict__ xm,
-                           double *__restrict__ gx, double *__restrict__ gm, int64_t n) {
+                           bool quad, const PosMass *__restrict__ xm,
+                           double *__restrict__ padj) {
     const int64_t leaf = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (leaf >= n_nodes || nchild[leaf] != 0) return;
     int32_t chain[kLevels + 1];
@@ -667,7 +706,7 @@ __global__ void k_vjp_down(int64_t n_nodes, const int32_t *__restrict__ nchild,
             const double e[3] = {mp[c].cx - mp[p].cx, mp[c].cy - mp[p].cy, mp[c].cz - mp[p].cz};
             form_shift(f, e);
         }
-        form_add_own(f, cadj + c, n_nodes, mp[c].M);
+        form_add_own(f, cadj + (int64_t)c * cell_adj(quad), quad, mp[c].M);
     }
     const double cx = mp[leaf].cx, cy = mp[leaf].cy, cz = mp[leaf].cz;
     const int32_t first = nw[leaf].first, cnt = nw[leaf].count;
@@ -676,25 +715,22 @@ __global__ void k_vjp_down(int64_t n_nodes, const int32_t *__restrict__ nchild,
         const double d[3] = {pk.x - cx, pk.y - cy, pk.z - cz};
         double Bd[3];
         Bmul(f.B, d, Bd);
-        gm[k] += d[0] * Bd[0] + d[1] * Bd[1] + d[2] * Bd[2] + f.b[0] * d[0] + f.b[1] * d[1] +
-                 f.b[2] * d[2] + f.g;
+        double *p = padj + 4 * (int64_t)k;
+        p[3] += d[0] * Bd[0] + d[1] * Bd[1] + d[2] * Bd[2] + f.b[0] * d[0] + f.b[1] * d[1] +
+                f.b[2] * d[2] + f.g;
         const double mk = pk.m;
-        gx[k] += mk * (2.0 * Bd[0] + f.b[0]);
-        gx[n + k] += mk * (2.0 * Bd[1] + f.b[1]);
-        gx[2 * n + k] += mk * (2.0 * Bd[2] + f.b[2]);
+        for (int a = 0; a < 3; ++a) p[a] += mk * (2.0 * Bd[a] + f.b[a]);
     }
 }
 
 __global__ void k_vjp_unpermute(int64_t n, const int32_t *__restrict__ perm,
-                                const double *__restrict__ gx, const double *__restrict__ gm,
-                                double *__restrict__ gpos, double *__restrict__ gmass) {
+                                const double *__restrict__ padj, double *__restrict__ gpos,
+                                double *__restrict__ gmass) {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n) return;
     const int64_t o = perm[s];
-    gpos[3 * o] = gx[s];
-    gpos[3 * o + 1] = gx[n + s];
-    gpos[3 * o + 2] = gx[2 * n + s];
-    gmass[o] = gm[s];
+    for (int a = 0; a < 3; ++a) gpos[3 * o + a] = padj[4 * s + a];
+    gmass[o] = padj[4 * s + 3];
 }
 
 __global__ void k_vjp_zero(int64_t count, double *__restrict__ a) {
@@ -705,15 +741,14 @@ __global__ void k_vjp_zero(int64_t count, double *__restrict__ a) {
 int launch_vjp(p3t_ctx *ctx, const double *w, const double *c, double *gpos, double *gmass) {
     int rc;
     const int64_t n = ctx->n, nn = ctx->n_nodes;
-    if ((rc = ensure(ctx, ctx->vjp_gx, 3 * n * sizeof(double)))) return rc;
-    if ((rc = ensure(ctx, ctx->vjp_gm, n * sizeof(double)))) return rc;
-    if ((rc = ensure(ctx, ctx->vjp_cell, 10 * nn * sizeof(double)))) return rc;
-    return launch_vjp_ws(ctx, w, c, gpos, gmass, ptr<double>(ctx->vjp_gx), ptr<double>(ctx->vjp_gm),
+    if ((rc = ensure(ctx, ctx->vjp_part, 4 * n * sizeof(double)))) return rc;
+    if ((rc = ensure(ctx, ctx->vjp_cell, cell_adj(true) * nn * sizeof(double)))) return rc;
+    return launch_vjp_ws(ctx, w, c, gpos, gmass, ptr<double>(ctx->vjp_part),
                          ptr<double>(ctx->vjp_cell));
 }
 
 int launch_vjp_ws(p3t_ctx *ctx, const double *w, const double *c, double *gpos, double *gmass,
-                  double *gx, double *gm, double *cadj) {
+                  double *padj, double *cadj) {
     int rc;
     const int64_t n = ctx->n, nn = ctx->n_nodes;
     VjpParams vp{};
@@ -731,7 +766,8 @@ int launch_vjp_ws(p3t_ctx *ctx, const double *w, const double *c, double *gpos, 
     const ListsDev L = lists_dev(ctx);
     // the cell adjoints are accumulated: clear them (a fill kernel, which a
     // caller's graph capture records as an ordinary kernel node)
-    k_vjp_zero<<<blocks_for(10 * nn, 256), 256, 0, ctx->stream>>>(10 * nn, cadj);
+    const int64_t words = cell_adj(vp.use_quad) * nn;
+    k_vjp_zero<<<blocks_for(words, 256), 256, 0, ctx->stream>>>(words, cadj);
     if ((rc = check_hip(ctx, hipGetLastError(), "vjp clear"))) return rc;
     // a group that the interaction kernel splits is shared by as many blocks here
     const unsigned blocks = (unsigned)work_blocks(ctx);
@@ -752,18 +788,18 @@ int launch_vjp_ws(p3t_ctx *ctx, const double *w, const double *c, double *gpos, 
                                       : k_vjp_scatter<double, false, false>));
     ki<<<blocks, kVjpThreads, 0, ctx->stream>>>(ptr<GroupInfo>(ctx->grp), L, wd,
                                                 ptr<PosMass>(ctx->xm), ptr<int32_t>(ctx->vals[0]),
-                                                w, c, vp, gx, gm, n);
+                                                w, c, vp, padj);
     if ((rc = check_hip(ctx, hipGetLastError(), "vjp i-side"))) return rc;
     ks<<<blocks, kVjpThreads, 0, ctx->stream>>>(
         ptr<GroupInfo>(ctx->grp), L, wd, ptr<PosMass>(ctx->xm), ptr<NodeMP>(ctx->node_mp),
-        ptr<int32_t>(ctx->vals[0]), w, c, vp, gx, gm, cadj, n, nn);
+        ptr<int32_t>(ctx->vals[0]), w, c, vp, padj, cadj);
     if ((rc = check_hip(ctx, hipGetLastError(), "vjp scatter"))) return rc;
     k_vjp_down<<<blocks_for(nn, 128), 128, 0, ctx->stream>>>(
         nn, ptr<int32_t>(ctx->node_nchild), ptr<int32_t>(ctx->node_parent), ptr<NodeMP>(ctx->node_mp),
-        ptr<NodeWalk>(ctx->node_walk), cadj, ptr<PosMass>(ctx->xm), gx, gm, n);
+        ptr<NodeWalk>(ctx->node_walk), cadj, quad, ptr<PosMass>(ctx->xm), padj);
     if ((rc = check_hip(ctx, hipGetLastError(), "vjp push-down"))) return rc;
-    k_vjp_unpermute<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(n, ptr<int32_t>(ctx->vals[0]), gx,
-                                                                 gm, gpos, gmass);
+    k_vjp_unpermute<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(n, ptr<int32_t>(ctx->vals[0]), padj,
+                                                                 gpos, gmass);
     return check_hip(ctx, hipGetLastError(), "vjp unpermute");
 }
 
