@@ -56,6 +56,13 @@ __device__ __forceinline__ int wave_excl_count(int v, int &total) {
     return incl - v;
 }
 
+// Orders this wavefront's LDS accesses before and after (the hardware completes
+// them in program order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // v from the lane that DPP control CTRL selects (0 where ROW_MASK disables
 // the row); for float and double
 template <int CTRL, int ROW_MASK = 0xf>

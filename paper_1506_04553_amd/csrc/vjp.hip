@@ -393,16 +393,12 @@ __host__ __device__ constexpr int cell_adj(bool quad) { return quad ? 9 : 4; }
 template <int N>
 __device__ __forceinline__ void scatter_add(double *buf, const double v[N], int32_t id, int lane,
                                             double *__restrict__ dst) {
-    auto in_order = [] {   // LDS accesses of one wavefront complete in program order
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    };
 #pragma unroll 1
     for (int r = 0; r < kWave; r += 16) {
-        in_order();
+        wave_order();
         if ((lane & 48) == r)
             for (int a = 0; a < N; ++a) buf[(lane & 15) * N + a] = v[a];
-        in_order();
+        wave_order();
 #pragma unroll
         for (int e0 = 0; e0 < 16 * N; e0 += kWave) {
             const int e = e0 + lane;

@@ -21,13 +21,14 @@ def ctx():
     c.close()
 
 
-def _components(rng, sizes, cliques, stars=0):
+def _components(rng, sizes, cliques, stars=0, isolated=0):
     """Members of each component around its own centre, shuffled over the arrays;
     every member lists the two beside it, or (the first `cliques`) all others, or
-    (the first `stars`) the two beside it and the first one, which lists all."""
-    n = int(sum(sizes))
+    (the first `stars`) the two beside it and the first one, which lists all.
+    `isolated` particles more list nothing."""
+    n = int(sum(sizes)) + isolated
     slot = rng.permutation(n)
-    pos, rows, b = np.empty((n, 3)), [None] * n, 0
+    pos, rows, b = rng.uniform(-9, -1, (n, 3)), [np.zeros(0, np.int64)] * n, 0
     for c, m in enumerate(sizes):
         me = slot[b:b + m]
         d = rng.uniform(-1e-3, 1e-3, (m, 3))
@@ -43,14 +44,20 @@ def _components(rng, sizes, cliques, stars=0):
     return pos, off, np.concatenate(rows).astype(np.int32)
 
 
-@pytest.mark.parametrize("sizes,cliques", [
-    ([63, 31, 32, 63, 64, 8, 1 + 6], 1),
-    ([63, 32, 64] + [32] * 511 + [63, 31, 31, 16, 15], 2),   # 515 of 32 and more
+@pytest.mark.parametrize("sizes,cliques,n", [
+    ([63, 31, 32, 63, 64, 8, 1 + 6], 1, 0),
+    ([63, 32, 64] + [32] * 511 + [63, 31, 31, 16, 15], 2, 0),   # 515 of 32 and more
+    # the search for components in one workgroup: its last n and the first beyond,
+    # and more list entries than it takes (370 x 369)
+    ([2] * 4000 + [7, 33, 3], 0, 16384),
+    ([2] * 4000 + [7, 33, 3], 0, 16385),
+    ([370, 2, 5], 1, 0),
+    ([2], 0, 2),
 ])
-def test_size_classes_match_oracle(ctx, sizes, cliques):
+def test_size_classes_match_oracle(ctx, sizes, cliques, n):
     import torch
     rng = np.random.default_rng(5)
-    pos, off, idx = _components(rng, sizes, cliques)
+    pos, off, idx = _components(rng, sizes, cliques, isolated=max(n - sum(sizes), 0))
     n = len(pos)
     vel = rng.normal(scale=0.02, size=(n, 3))
     mass = rng.uniform(0.5e-6, 1.5e-6, n)
@@ -69,15 +76,17 @@ def test_size_classes_match_oracle(ctx, sizes, cliques):
     assert np.array_equal(x.cpu().numpy(), ox) and np.array_equal(v.cpu().numpy(), ov)
 
 
-@pytest.mark.parametrize("special", [0, 3])
-def test_giant_components_match_oracle(ctx, special):
+@pytest.mark.parametrize("special,isolated", [(0, 0), (3, 0), (0, 13000)])
+def test_giant_components_match_oracle(ctx, special, isolated):
     """Components that advance by grid-wide launches, at the edges of their class
     (1024 members, and 1023 beside them), with the members of three of them in one
     run of 64, with rows longer than a workgroup takes at a time, with a component
-    that needs far fewer block steps than the other, and with special particles."""
+    that needs far fewer block steps than the other, with special particles, and
+    beside so many isolated ones that the components are found by many launches."""
     import torch
     rng = np.random.default_rng(6)
-    pos, off, idx = _components(rng, [1101, 1024, 1025, 1023, 2, 40], 0, stars=1)
+    pos, off, idx = _components(rng, [1101, 1024, 1025, 1023, 2, 40], 0, stars=1,
+                                isolated=isolated)
     n = len(pos)
     vel = rng.normal(scale=0.02, size=(n, 3))
     mass = rng.uniform(0.5e-6, 1.5e-6, n)
