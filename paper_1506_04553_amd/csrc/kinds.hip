@@ -14,7 +14,9 @@
 //     the other special particles (all of them when their pair is not split),
 //     every row ascending.
 // Special particles are few (the paper uses two), so one block per special
-// particle sweeps the normal particles.
+// particle sweeps the normal particles, in the launch whose other blocks take a
+// normal particle per thread: these sweeps are as short as launches are for a few
+// thousand particles.
 #include <math.h>
 
 #include "device_util.h"
@@ -22,7 +24,8 @@
 
 namespace p3t {
 
-constexpr int kKindThreads = 256;
+constexpr int kKindThreads = 1024;
+constexpr int kKindWaves = kKindThreads / kWave;
 
 // constants of one kind of pair for the soft sums
 struct SoftPair {
@@ -83,43 +86,43 @@ __device__ inline void soft_pull(const double *xi, const double *xj, double mj, 
     ph -= mj * Ws;
 }
 
-// normal particles: add the pulls of the special particles
-__global__ __launch_bounds__(kKindThreads) void k_kinds_soft_normal(
-    const double *__restrict__ pos, const double *__restrict__ mass, KindsConsts kc,
-    double *__restrict__ acc, double *__restrict__ pot) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kc.first_sp) return;
-    double a[3] = {0.0, 0.0, 0.0}, ph = 0.0;
-    for (int64_t b = kc.first_sp; b < kc.n; ++b) soft_pull(pos + 3 * i, pos + 3 * b, mass[b], kc.ns, a, ph);
-    for (int q = 0; q < 3; ++q) acc[3 * i + q] += a[q];
-    if (pot) pot[i] += ph;
+// Blocks of normal particles come first, then one for each special particle.
+__host__ __device__ inline int64_t normal_blocks(int64_t first_sp) {
+    return (first_sp + kKindThreads - 1) / kKindThreads;
 }
 
-// special particle first_sp + blockIdx.x: the pulls of every other particle
-__global__ __launch_bounds__(kKindThreads) void k_kinds_soft_special(
+// normal particles: add the pulls of the special particles; special particles:
+// the pulls of every other particle, summed over the block
+__global__ __launch_bounds__(kKindThreads) void k_kinds_soft(
     const double *__restrict__ pos, const double *__restrict__ mass, KindsConsts kc,
     double *__restrict__ acc, double *__restrict__ pot) {
-    __shared__ double s_r[4][kKindThreads];
-    const int64_t b = kc.first_sp + blockIdx.x;
-    double a[3] = {0.0, 0.0, 0.0}, ph = 0.0;
+    __shared__ double s_r[kKindWaves][4];
+    const int64_t nb = normal_blocks(kc.first_sp);
+    double r[4] = {0.0, 0.0, 0.0, 0.0};          // a and phi
+    if (blockIdx.x < nb) {
+        const int64_t i = (int64_t)blockIdx.x * kKindThreads + threadIdx.x;
+        if (i >= kc.first_sp) return;
+        for (int64_t b = kc.first_sp; b < kc.n; ++b)
+            soft_pull(pos + 3 * i, pos + 3 * b, mass[b], kc.ns, r, r[3]);
+        for (int q = 0; q < 3; ++q) acc[3 * i + q] += r[q];
+        if (pot) pot[i] += r[3];
+        return;
+    }
+    const int64_t b = kc.first_sp + (blockIdx.x - nb);
     for (int64_t j = threadIdx.x; j < kc.n; j += kKindThreads) {
         if (j == b) continue;
-        soft_pull(pos + 3 * b, pos + 3 * j, mass[j], j >= kc.first_sp ? kc.ss : kc.ns, a, ph);
+        soft_pull(pos + 3 * b, pos + 3 * j, mass[j], j >= kc.first_sp ? kc.ss : kc.ns, r, r[3]);
     }
-    s_r[0][threadIdx.x] = a[0];
-    s_r[1][threadIdx.x] = a[1];
-    s_r[2][threadIdx.x] = a[2];
-    s_r[3][threadIdx.x] = ph;
+    for (int q = 0; q < 4; ++q) {
+        r[q] = wave_sum(r[q]);
+        if (threadIdx.x % kWave == 0) s_r[threadIdx.x / kWave][q] = r[q];
+    }
     __syncthreads();
-    for (int w = kKindThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int q = 0; q < 4; ++q) s_r[q][threadIdx.x] += s_r[q][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        for (int q = 0; q < 3; ++q) acc[3 * b + q] = s_r[q][0];
-        if (pot) pot[b] = s_r[3][0];
-    }
+    if (threadIdx.x >= 4) return;
+    double t = 0.0;
+    for (int w = 0; w < kKindWaves; ++w) t += s_r[w][threadIdx.x];
+    if (threadIdx.x < 3) acc[3 * b + threadIdx.x] = t;
+    else if (pot) pot[b] = t;
 }
 
 // ---------------------------------------------------------------------------
@@ -141,71 +144,75 @@ __device__ inline bool ss_listed(const double *pos, int64_t b, int64_t c, const 
     return c != b && (!kn.split_ss || within(pos + 3 * b, pos + 3 * c, kn.h2_ss));
 }
 
-__global__ __launch_bounds__(kKindThreads) void k_kn_count_normal(
-    const double *__restrict__ pos, const int64_t *__restrict__ nn_off, KindsNbr kn,
-    int64_t *__restrict__ cnt) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kn.first_sp) return;
-    int64_t c = nn_off[i + 1] - nn_off[i];
-    for (int64_t b = kn.first_sp; b < kn.n; ++b) c += within(pos + 3 * i, pos + 3 * b, kn.h2_ns);
-    cnt[i] = c;
-}
-
-__global__ __launch_bounds__(kKindThreads) void k_kn_count_special(const double *__restrict__ pos,
-                                                                   KindsNbr kn,
-                                                                   int64_t *__restrict__ cnt) {
-    __shared__ int64_t s_c[kKindThreads];
-    const int64_t b = kn.first_sp + blockIdx.x;
+// row lengths; cnt[n] = 0 for the scan
+__global__ __launch_bounds__(kKindThreads) void k_kn_count(const double *__restrict__ pos,
+                                                           const int64_t *__restrict__ nn_off,
+                                                           KindsNbr kn, int64_t *__restrict__ cnt) {
+    __shared__ int64_t s_c[kKindWaves];
+    const int64_t nb = normal_blocks(kn.first_sp);
+    if (blockIdx.x == 0 && threadIdx.x == 0) cnt[kn.n] = 0;
     int64_t c = 0;
+    if (blockIdx.x < nb) {
+        const int64_t i = (int64_t)blockIdx.x * kKindThreads + threadIdx.x;
+        if (i >= kn.first_sp) return;
+        c = nn_off[i + 1] - nn_off[i];
+        for (int64_t b = kn.first_sp; b < kn.n; ++b)
+            c += within(pos + 3 * i, pos + 3 * b, kn.h2_ns);
+        cnt[i] = c;
+        return;
+    }
+    const int64_t b = kn.first_sp + (blockIdx.x - nb);
     for (int64_t j = threadIdx.x; j < kn.first_sp; j += kKindThreads)
         c += within(pos + 3 * b, pos + 3 * j, kn.h2_ns);
-    for (int64_t j = kn.first_sp + threadIdx.x; j < kn.n; j += kKindThreads) c += ss_listed(pos, b, j, kn);
-    s_c[threadIdx.x] = c;
+    for (int64_t j = kn.first_sp + threadIdx.x; j < kn.n; j += kKindThreads)
+        c += ss_listed(pos, b, j, kn);
+    c = wave_sum(c);
+    if (threadIdx.x % kWave == 0) s_c[threadIdx.x / kWave] = c;
     __syncthreads();
-    for (int w = kKindThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) s_c[threadIdx.x] += s_c[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) cnt[b] = s_c[0];
+    if (threadIdx.x != 0) return;
+    c = 0;
+    for (int w = 0; w < kKindWaves; ++w) c += s_c[w];
+    cnt[b] = c;
 }
 
-__global__ __launch_bounds__(kKindThreads) void k_kn_fill_normal(
+// The rows, ascending, and the caller's offsets.  A special particle's row is an
+// ordered compaction of the hits over chunks of the block.
+__global__ __launch_bounds__(kKindThreads) void k_kn_fill(
     const double *__restrict__ pos, const int64_t *__restrict__ nn_off,
-    const int32_t *__restrict__ nn_idx, KindsNbr kn, const int64_t *__restrict__ off,
-    int32_t *__restrict__ idx) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kn.first_sp) return;
-    int64_t o = off[i];
-    for (int64_t e = nn_off[i]; e < nn_off[i + 1]; ++e) idx[o++] = nn_idx[e];
-    for (int64_t b = kn.first_sp; b < kn.n; ++b)
-        if (within(pos + 3 * i, pos + 3 * b, kn.h2_ns)) idx[o++] = (int32_t)b;
-}
-
-// special particle b's row, ascending: an ordered compaction of the hits over
-// chunks of the block
-__global__ __launch_bounds__(kKindThreads) void k_kn_fill_special(const double *__restrict__ pos,
-                                                                  KindsNbr kn,
-                                                                  const int64_t *__restrict__ off,
-                                                                  int32_t *__restrict__ idx) {
-    __shared__ int s_scan[kKindThreads];
-    const int64_t b = kn.first_sp + blockIdx.x;
-    int64_t o = off[b];
-    for (int64_t j0 = 0; j0 < kn.n; j0 += kKindThreads) {
+    const int32_t *__restrict__ nn_idx, KindsNbr kn, const int64_t *__restrict__ start,
+    int64_t *__restrict__ off, int32_t *__restrict__ idx) {
+    __shared__ int s_hits[2][kKindWaves];
+    const int64_t nb = normal_blocks(kn.first_sp);
+    if (blockIdx.x == 0 && threadIdx.x == 0) off[kn.n] = start[kn.n];
+    if (blockIdx.x < nb) {
+        const int64_t i = (int64_t)blockIdx.x * kKindThreads + threadIdx.x;
+        if (i >= kn.first_sp) return;
+        int64_t o = start[i];
+        off[i] = o;
+        for (int64_t e = nn_off[i]; e < nn_off[i + 1]; ++e) idx[o++] = nn_idx[e];
+        for (int64_t b = kn.first_sp; b < kn.n; ++b)
+            if (within(pos + 3 * i, pos + 3 * b, kn.h2_ns)) idx[o++] = (int32_t)b;
+        return;
+    }
+    const int64_t b = kn.first_sp + (blockIdx.x - nb);
+    const int w = threadIdx.x / kWave;
+    int64_t o = start[b];
+    if (threadIdx.x == 0) off[b] = o;
+    int side = 0;   // the counts of two chunks in turn: one barrier per chunk
+    for (int64_t j0 = 0; j0 < kn.n; j0 += kKindThreads, side ^= 1) {
         const int64_t j = j0 + threadIdx.x;
-        int hit = 0;
+        bool hit = false;
         if (j < kn.first_sp) hit = within(pos + 3 * b, pos + 3 * j, kn.h2_ns);
         else if (j < kn.n) hit = ss_listed(pos, b, j, kn);
-        s_scan[threadIdx.x] = hit;
+        const uint64_t hits = ballot(hit);
+        if (threadIdx.x % kWave == 0) s_hits[side][w] = __popcll(hits);
         __syncthreads();
-        for (int w = 1; w < kKindThreads; w <<= 1) {   // inclusive scan
-            const int v = (int)threadIdx.x >= w ? s_scan[threadIdx.x - w] : 0;
-            __syncthreads();
-            s_scan[threadIdx.x] += v;
-            __syncthreads();
+        int64_t at = o + count_below(hits);
+        for (int v = 0; v < kKindWaves; ++v) {
+            at += v < w ? s_hits[side][v] : 0;
+            o += s_hits[side][v];
         }
-        if (hit) idx[o + s_scan[threadIdx.x] - 1] = (int32_t)j;
-        o += s_scan[kKindThreads - 1];
-        __syncthreads();
+        if (hit) idx[at] = (int32_t)j;
     }
 }
 
@@ -223,11 +230,8 @@ int launch_kinds_soft(p3t_ctx *ctx, int64_t n, const double *pos, const double *
     (void)p;
     if (!kd || kd->n_special == 0) return P3T_OK;
     const KindsConsts kc = kinds_consts(n, kd);
-    if (kc.first_sp > 0)
-        k_kinds_soft_normal<<<blocks_for(kc.first_sp, kKindThreads), kKindThreads, 0, ctx->stream>>>(
-            pos, mass, kc, acc, pot);
-    k_kinds_soft_special<<<(unsigned)kd->n_special, kKindThreads, 0, ctx->stream>>>(pos, mass, kc,
-                                                                                  acc, pot);
+    k_kinds_soft<<<(unsigned)(normal_blocks(kc.first_sp) + kd->n_special), kKindThreads, 0,
+                   ctx->stream>>>(pos, mass, kc, acc, pot);
     return check_hip(ctx, hipGetLastError(), "kinds soft");
 }
 
@@ -248,13 +252,9 @@ int launch_kinds_neighbors(p3t_ctx *ctx, int64_t n, const double *pos, const p3t
     kn.split_ss = kd->split_ss;
     kn.first_sp = n - kd->n_special;
     kn.n = n;
-    if (kn.first_sp > 0)
-        k_kn_count_normal<<<blocks_for(kn.first_sp, kKindThreads), kKindThreads, 0, st>>>(
-            pos, nn_off, kn, cnt);
-    if (kd->n_special > 0)
-        k_kn_count_special<<<(unsigned)kd->n_special, kKindThreads, 0, st>>>(pos, kn, cnt);
+    const unsigned blocks = (unsigned)(normal_blocks(kn.first_sp) + kd->n_special);
+    k_kn_count<<<blocks, kKindThreads, 0, st>>>(pos, nn_off, kn, cnt);
     if ((rc = check_hip(ctx, hipGetLastError(), "kinds count"))) return rc;
-    if ((rc = check_hip(ctx, hipMemsetAsync(cnt + n, 0, sizeof(int64_t), st), "memset"))) return rc;
     if ((rc = scan_exclusive_i64(ctx, cnt, cnt, n + 1, rb + RB_KNNZ))) return rc;
     if ((rc = check_hip(ctx, hipMemcpyAsync(ctx->hpin + RB_KNNZ, rb + RB_KNNZ, sizeof(int64_t),
                                             hipMemcpyDeviceToHost, st), "readback")))
@@ -265,14 +265,7 @@ int launch_kinds_neighbors(p3t_ctx *ctx, int64_t n, const double *pos, const p3t
     if (total > cap)
         return set_error(ctx, P3T_ECAPACITY, "neighbour capacity %lld < %lld", (long long)cap,
                          (long long)total);
-    if ((rc = check_hip(ctx, hipMemcpyAsync(off, cnt, (size_t)(n + 1) * sizeof(int64_t),
-                                            hipMemcpyDeviceToDevice, st), "copy")))
-        return rc;
-    if (kn.first_sp > 0)
-        k_kn_fill_normal<<<blocks_for(kn.first_sp, kKindThreads), kKindThreads, 0, st>>>(
-            pos, nn_off, nn_idx, kn, cnt, idx);
-    if (kd->n_special > 0)
-        k_kn_fill_special<<<(unsigned)kd->n_special, kKindThreads, 0, st>>>(pos, kn, cnt, idx);
+    k_kn_fill<<<blocks, kKindThreads, 0, st>>>(pos, nn_off, nn_idx, kn, cnt, off, idx);
     return check_hip(ctx, hipGetLastError(), "kinds fill");
 }
 
