@@ -160,8 +160,8 @@ int scan_exclusive_i32(p3t_ctx *ctx, const int32_t *in, int32_t *out, int64_t n,
 // The same on stream st with the workspace tmp (at least scan_tmp_bytes(n)
 // bytes, so that the call allocates nothing).
 size_t scan_tmp_bytes(int64_t n);
-int scan_exclusive_i64_on(p3t_ctx *ctx, hipStream_t st, DevBuf &tmp, const int64_t *in,
-                          int64_t *out, int64_t n, int64_t *total);
+int scan_exclusive_i64_on(p3t_ctx *ctx, hipStream_t st, DevBuf &tmp, const int64_t *in, int64_t *out,
+                          int64_t n, int64_t *total, const int64_t *from, int64_t *to, int words);
 // Exclusive prefix sum of each row of a [rows][cols] array (one block per
 // row, one launch); totals[r] receives the sum of row r.
 int scan_rows_i32(p3t_ctx *ctx, const int32_t *in, int32_t *out, int32_t *totals, int rows,

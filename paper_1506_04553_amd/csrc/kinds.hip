@@ -245,7 +245,7 @@ int launch_kinds_neighbors(p3t_ctx *ctx, int64_t n, const double *pos, const p3t
     hipStream_t st = ctx->stream;
     if ((rc = ensure_readback(ctx))) return rc;
     if ((rc = ensure(ctx, ctx->kinds_cnt, (size_t)(n + 1) * sizeof(int64_t)))) return rc;
-    int64_t *cnt = ptr<int64_t>(ctx->kinds_cnt), *rb = ptr<int64_t>(ctx->readback);
+    int64_t *cnt = ptr<int64_t>(ctx->kinds_cnt);
     KindsNbr kn;
     kn.h2_ns = kd->r_search_ns * kd->r_search_ns;
     kn.h2_ss = kd->r_search_ss * kd->r_search_ss;
@@ -255,10 +255,7 @@ int launch_kinds_neighbors(p3t_ctx *ctx, int64_t n, const double *pos, const p3t
     const unsigned blocks = (unsigned)(normal_blocks(kn.first_sp) + kd->n_special);
     k_kn_count<<<blocks, kKindThreads, 0, st>>>(pos, nn_off, kn, cnt);
     if ((rc = check_hip(ctx, hipGetLastError(), "kinds count"))) return rc;
-    if ((rc = scan_exclusive_i64(ctx, cnt, cnt, n + 1, rb + RB_KNNZ))) return rc;
-    if ((rc = check_hip(ctx, hipMemcpyAsync(ctx->hpin + RB_KNNZ, rb + RB_KNNZ, sizeof(int64_t),
-                                            hipMemcpyDeviceToHost, st), "readback")))
-        return rc;
+    if ((rc = scan_exclusive_i64(ctx, cnt, cnt, n + 1, ctx->hpin + RB_KNNZ))) return rc;
     if ((rc = check_hip(ctx, hipStreamSynchronize(st), "sync"))) return rc;
     const int64_t total = ctx->hpin[RB_KNNZ];
     *nnz = total;

@@ -227,10 +227,9 @@ int launch_neighbors(p3t_ctx *ctx, int64_t *offsets, int32_t *idx, int64_t cap, 
         ptr<GroupInfo>(ctx->grp), L, ptr<PosMass>(ctx->xm), ptr<int32_t>(ctx->vals[0]), h2, row_cap,
         ptr<int32_t>(ctx->nbr_slots), nullptr, cnt, n, tag, rbu + RB_NMAX, rbu + RB_NOVF);
     if ((rc = check_hip(ctx, hipGetLastError(), "neighbours"))) return rc;
-    if ((rc = scan_exclusive_i64_on(ctx, as, ctx->nbr_scan, cnt, cnt, n + 1, rb + RB_NNZ)))
-        return rc;
-    if ((rc = check_hip(ctx, hipMemcpyAsync(ctx->hpin + RB_NNZ, rb + RB_NNZ, 3 * sizeof(int64_t),
-                                            hipMemcpyDeviceToHost, as), "readback")))
+    // (the scan writes the total and the two words to the host's readback area)
+    if ((rc = scan_exclusive_i64_on(ctx, as, ctx->nbr_scan, cnt, cnt, n + 1, ctx->hpin + RB_NNZ,
+                                    rb + RB_NOVF, ctx->hpin + RB_NOVF, 2)))
         return rc;
     if (t1 && (rc = check_hip(ctx, hipEventRecord(t1, as), "event record"))) return rc;
     if ((rc = check_hip(ctx, hipEventRecord(ctx->ev_sync[1], as), "event record"))) return rc;

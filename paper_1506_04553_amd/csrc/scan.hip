@@ -89,7 +89,8 @@ constexpr int kScanOneItems = 16;
 constexpr int64_t kScanOneMax = kScanOneThreads * kScanOneItems;
 
 template <class T>
-__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const T *in, T *out, int n, T *total) {
+__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const T *in, T *out, int n,
+                                                             ScanTail<T> tail) {
     __shared__ T wsum[kScanOneThreads / kWave];
     const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
     const int per = (n + kScanOneThreads - 1) / kScanOneThreads, base = tid * per;
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const T *in, T *ou
         if (k < per && base + k < n) out[base + k] = excl;
         excl += v[k];
     }
-    if (total && tid == 0) *total = all;
+    tail(tid, all);
 }
 
 static bool scan_two_pass(int64_t n) {
@@ -133,22 +134,26 @@ size_t scan_tmp_bytes(int64_t n) {
 
 template <class T>
 static int scan_any(p3t_ctx *ctx, hipStream_t st, DevBuf &tmp, const T *in, T *out, int64_t n,
-                    T *total) {
+                    const ScanTail<T> &tail) {
     int rc = ensure(ctx, tmp, scan_tmp_bytes(n));
     if (rc) return rc;
     if (n > 0 && n <= kScanOneMax) {
-        k_scan_one<T><<<1, kScanOneThreads, 0, st>>>(in, out, (int)n, total);
+        k_scan_one<T><<<1, kScanOneThreads, 0, st>>>(in, out, (int)n, tail);
         return check_hip(ctx, hipGetLastError(), "scan");
     }
     if (scan_two_pass(n)) {
         const unsigned tiles = (unsigned)((n + kScan2Tile - 1) / kScan2Tile);
         T *sums = ptr<T>(tmp);
         k_scan2_sums<T><<<tiles, kScanThreads, 0, st>>>(in, n, sums);
-        k_scan2_tiles<T><<<tiles, kScanThreads, 0, st>>>(in, n, sums, total,
+        k_scan2_tiles<T><<<tiles, kScanThreads, 0, st>>>(in, n, sums, tail,
                                                          StoreExclusive<T>{out});
         return check_hip(ctx, hipGetLastError(), "scan");
     }
-    return scan_rec<T>(ctx, st, in, out, n, total, ptr<T>(tmp));
+    if (tail.words > 0 &&
+        (rc = check_hip(ctx, hipMemcpyAsync(tail.to, tail.from, tail.words * sizeof(int64_t),
+                                            hipMemcpyDefault, st), "scan")))
+        return rc;
+    return scan_rec<T>(ctx, st, in, out, n, tail.total, ptr<T>(tmp));
 }
 
 // Block r: exclusive scan of row r in chunks of kScanThreads with a running carry.
@@ -186,16 +191,17 @@ int scan_rows_i32(p3t_ctx *ctx, const int32_t *in, int32_t *out, int32_t *totals
 }
 
 int scan_exclusive_i64(p3t_ctx *ctx, const int64_t *in, int64_t *out, int64_t n, int64_t *total) {
-    return scan_any<int64_t>(ctx, ctx->stream, ctx->scan_tmp, in, out, n, total);
+    return scan_any<int64_t>(ctx, ctx->stream, ctx->scan_tmp, in, out, n, {total});
 }
 
 int scan_exclusive_i32(p3t_ctx *ctx, const int32_t *in, int32_t *out, int64_t n, int32_t *total) {
-    return scan_any<int32_t>(ctx, ctx->stream, ctx->scan_tmp, in, out, n, total);
+    return scan_any<int32_t>(ctx, ctx->stream, ctx->scan_tmp, in, out, n, {total});
 }
 
 int scan_exclusive_i64_on(p3t_ctx *ctx, hipStream_t st, DevBuf &tmp, const int64_t *in,
-                          int64_t *out, int64_t n, int64_t *total) {
-    return scan_any<int64_t>(ctx, st, tmp, in, out, n, total);
+                          int64_t *out, int64_t n, int64_t *total, const int64_t *from, int64_t *to,
+                          int words) {
+    return scan_any<int64_t>(ctx, st, tmp, in, out, n, {total, from, to, words});
 }
 
 }  // namespace p3t

@@ -35,11 +35,26 @@ __global__ __launch_bounds__(kScan2Threads) void k_scan2_sums(const T *__restric
     }
 }
 
-// sink(i, prefix, value) for every i < n; *total (if given) = the sum of all
+// What a scan leaves beside its prefixes: the sum of all in *total (if given), and
+// `words` words copied from `from` to `to`, which may be pinned host memory: the
+// results of the work before it, without a copy of its own.
+template <class T>
+struct ScanTail {
+    T *total = nullptr;
+    const int64_t *from = nullptr;
+    int64_t *to = nullptr;
+    int words = 0;
+    __device__ __forceinline__ void operator()(int tid, T sum) const {
+        if (tid < words) to[tid] = from[tid];
+        if (tid == 0 && total) *total = sum;
+    }
+};
+
+// sink(i, prefix, value) for every i < n
 template <class T, class Sink>
 __global__ __launch_bounds__(kScan2Threads) void k_scan2_tiles(const T *in, int64_t n,
                                                                const T *__restrict__ tile_sums,
-                                                               T *total, Sink sink) {
+                                                               ScanTail<T> tail, Sink sink) {
     __shared__ T wsum[kScan2Threads / kWave];
     __shared__ T s_base;
     const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
@@ -53,9 +68,9 @@ __global__ __launch_bounds__(kScan2Threads) void k_scan2_tiles(const T *in, int6
         T s = 0;
         for (int k = 0; k < kScan2Threads / kWave; ++k) s += wsum[k];
         s_base = s;
-        if (total && blockIdx.x == gridDim.x - 1) *total = s + tile_sums[blockIdx.x];
     }
     __syncthreads();
+    if (blockIdx.x == gridDim.x - 1) tail(tid, s_base + tile_sums[blockIdx.x]);
     // the tile: each thread scans kScan2Items consecutive elements
     const int64_t base = (int64_t)blockIdx.x * kScan2Tile + (int64_t)tid * kScan2Items;
     T v[kScan2Items];

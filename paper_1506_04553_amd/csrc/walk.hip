@@ -214,7 +214,7 @@ struct WalkStats {
     int32_t stack_ovf, cap_ovf;    // flags written by the walk
     int32_t spilled, n_items;      // groups that needed the global stack; items of split groups
     unsigned long long part_used;  // partial sums handed out to split groups
-    unsigned long long pad[2];
+    unsigned long long blocks_done, pad;   // blocks of the statistics kernel
     // per launch-order bucket (see below): groups, their cost, and what their
     // partial sums would take if they were split (FP32: exactly; FP64: members
     // times cost)
@@ -261,7 +261,8 @@ __global__ __launch_bounds__(1024) void k_walk_stats(const GroupInfo *__restrict
                                                     const int32_t *__restrict__ nchild,
                                                     int64_t n_nodes, bool wide,
                                                     WalkStats *__restrict__ out,
-                                                    int32_t *__restrict__ rank) {
+                                                    int32_t *__restrict__ rank,
+                                                    unsigned long long *__restrict__ host) {
     __shared__ unsigned long long s_cost[kOrderBins], s_room[kOrderBins], s_rounds[kOrderBins];
     __shared__ uint32_t s_bin[kOrderBins];
     const int G = *n_groups_dev;
@@ -339,6 +340,19 @@ __global__ __launch_bounds__(1024) void k_walk_stats(const GroupInfo *__restrict
         }
     }
     if (t0 == 0) out->n_groups = (unsigned long long)G;
+    // the last block hands the sums to the host's readback area
+    __shared__ bool s_last;
+    if (threadIdx.x < kOrderBins) __threadfence();   // the threads that added to it
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        s_last = atomicAdd(&out->blocks_done, 1ull) + 1 == gridDim.x;
+        __threadfence();
+    }
+    __syncthreads();
+    if (!s_last) return;
+    const unsigned long long *from = reinterpret_cast<const unsigned long long *>(out);
+    for (int k = threadIdx.x; k < kRbWalkWords; k += blockDim.x)
+        host[k] = __hip_atomic_load(&from[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 static unsigned walk_grid(p3t_ctx *ctx) {
@@ -544,12 +558,9 @@ static int run_walk_stats(p3t_ctx *ctx, const int32_t *G_dev, int64_t stride, Wa
     k_walk_stats<<<(unsigned)(fit < 32 ? fit : 32), 1024, 0, ctx->stream>>>(
         ptr<GroupInfo>(ctx->grp), G_dev, ptr<int64_t>(ctx->cnt), stride,
         ptr<int32_t>(ctx->node_nchild), ctx->n_nodes, ctx->prm.precision == P3T_PREC_FP64, ws,
-        ptr<int32_t>(ctx->grank));
+        ptr<int32_t>(ctx->grank), reinterpret_cast<unsigned long long *>(ctx->hpin + kRbWalk));
     int rc = check_hip(ctx, hipGetLastError(), "walk stats");
     if (rc) return rc;
-    if ((rc = check_hip(ctx, hipMemcpyAsync(ctx->hpin + kRbWalk, ws, sizeof(WalkStats),
-                                            hipMemcpyDeviceToHost, ctx->stream), "readback")))
-        return rc;
     return check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync");
 }
 
