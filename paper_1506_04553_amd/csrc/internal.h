@@ -110,6 +110,7 @@ struct p3t_ctx {
     int64_t *hpin = nullptr;      // pinned host readback area (kReadbackWords int64)
     void *scratch = nullptr;      // device address of the library's static workspace on this device
 
+    int64_t whole_sort_n = -1;    // particles of the builds that sort whole keys (tree.hip)
     p3t::DevBuf root, keys[2], vals[2], hist, histc, rs_tot, xm, xm_in;
     p3t::DevBuf lvlrange, tblk, tblk_off, gtile;
     p3t::DevBuf node_level, node_first, node_count, node_child, node_nchild, node_parent,
@@ -168,8 +169,10 @@ int scan_rows_i32(p3t_ctx *ctx, const int32_t *in, int32_t *out, int32_t *totals
                   int64_t cols);
 
 // Readback slots (int64 words of ctx->readback / ctx->hpin) written during a
-// build: the node count of each level (kLevels int32), then the input check.
+// build: the node count of each level (kLevels int32), then the input check, and
+// whether the short sort met a run of keys that it leaves unsorted.
 constexpr int kRbTopoBad = kLevels + 1;
+constexpr int kRbSortLonger = kLevels + 2;
 // The walk's statistics from this slot on (kRbWalkWords words, cleared by the
 // moments of the leaves before every walk of a build).
 constexpr int kRbWalk = 64;
@@ -179,8 +182,10 @@ static_assert(kRbWalk + kRbWalkWords <= kReadbackWords, "readback layout");
 // Tree build stages (tree.hip).
 // root cube, Morton keys, stable sort (keys[0] / vals[0]) and the sorted
 // particle records xm
-int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n);
-int build_topology(p3t_ctx *ctx, int64_t n);    // sets ctx->n_nodes, level_start, depth
+int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n, bool whole);
+// sets ctx->n_nodes, level_start, depth; or *unsorted, where the keys still have to
+// be sorted whole
+int build_topology(p3t_ctx *ctx, int64_t n, bool *unsorted);
 int build_moments(p3t_ctx *ctx);
 int build_groups(p3t_ctx *ctx);                 // sets ctx->n_groups
 

@@ -257,8 +257,15 @@ extern "C" int p3t_build_tree(p3t_ctx *ctx, int64_t n, const double *pos, const 
     ctx->chg = make_changeover(p->r_in, p->r_out);
     if ((rc = ensure_readback(ctx))) return rc;
     if ((rc = mark(ctx, EV_BUILD))) return rc;
-    if ((rc = build_sorted(ctx, pos, mass, n))) return rc;
-    if ((rc = build_topology(ctx, n))) return rc;
+    // (where the short sort didn't do, the next builds of as many particles don't try)
+    bool unsorted = false;
+    if ((rc = build_sorted(ctx, pos, mass, n, ctx->whole_sort_n == n))) return rc;
+    if ((rc = build_topology(ctx, n, &unsorted))) return rc;
+    if (unsorted) {
+        ctx->whole_sort_n = n;
+        if ((rc = build_sorted(ctx, pos, mass, n, true))) return rc;
+        if ((rc = build_topology(ctx, n, &unsorted))) return rc;
+    }
     if ((rc = build_moments(ctx))) return rc;
     if ((rc = build_groups(ctx))) return rc;
     if ((rc = mark(ctx, EV_WALK))) return rc;

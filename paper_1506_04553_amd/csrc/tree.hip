@@ -122,6 +122,14 @@ constexpr int kRsWaves = kRsThreads / kWave;
 constexpr int kRsBits = 8;                         // digit width: 8 passes cover the 63 key bits
 constexpr int kRsBins = 1 << kRsBits;
 constexpr int kRsPasses = (3 * kMaxLevel + kRsBits - 1) / kRsBits;
+// Few particles share the leading 40 bits of their keys (13 of 21 levels): runs
+// of at most 5 in a King W0 = 9 cluster of 2^20 stars, 10 in one of 2^22.  Five
+// passes over those bits and one that orders each run by the rest save three
+// passes: the sort's kernels take 162 us instead of 218 at 2^20 particles and 86
+// instead of 128 at 65536.  A run of more than kRsRun starts all eight passes instead.
+constexpr int kRsTopPasses = 5;
+constexpr int kRsTopShift = 3 * kMaxLevel - kRsTopPasses * kRsBits;
+constexpr int kRsRun = 64;
 constexpr int kRsPer = kRsBins / kRsThreads;       // digits per thread in the bookkeeping
 static_assert(kRsBins % kRsThreads == 0, "whole digits per thread");
 
@@ -151,7 +159,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const uint64_t *__restri
 }
 
 // Morton keys of the tile of kRsTile particles of this block, their indices,
-// the tile's histogram of the first radix digit (the keys' low bits), and each
+// the tile's histogram of the first radix digit (at `shift`), and each
 // particle's position and mass packed in one 32-byte record (xm_in, input
 // order) for the sort's final gather
 // The root cube from the bounding box's nbb (<= kRsThreads) block records, by
@@ -240,7 +248,7 @@ __global__ __launch_bounds__(kRsThreads) void k_keys_hist(const double *__restri
                                                           int64_t *__restrict__ bad_rb,
                                                           uint64_t *__restrict__ keys,
                                                           int32_t *__restrict__ idx,
-                                                          PosMass *__restrict__ xm_in,
+                                                          PosMass *__restrict__ xm_in, int shift,
                                                           int32_t *__restrict__ counts, int nb) {
     __shared__ int32_t h[kRsBins];
     for (int d = threadIdx.x; d < kRsBins; d += kRsThreads) h[d] = 0;
@@ -263,7 +271,7 @@ __global__ __launch_bounds__(kRsThreads) void k_keys_hist(const double *__restri
         keys[i] = key;
         idx[i] = (int32_t)i;
         xm_in[i] = r[k];
-        atomicAdd(&h[rs_digit(key, 0)], 1);
+        atomicAdd(&h[rs_digit(key, shift)], 1);
     }
     __syncthreads();
     for (int d = threadIdx.x; d < kRsBins; d += kRsThreads)
@@ -394,6 +402,49 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
         }
     }
     if (LAST && blockIdx.x == 0 && tid == 0) so.gflag[n] = 0;
+}
+
+// The last step of the short sort: keys ordered by their leading bits, stably, to
+// keys ordered whole, with the sorted particle records and cleared group-start
+// flags of the last radix pass.  A particle of a run of equal leading bits counts
+// the keys of the run that go before its own; one of a run of more than kRsRun
+// (all of its particles see that) stays where it is and says so in *longer.
+constexpr int kRsFinish = 256;
+__global__ __launch_bounds__(kRsFinish) void k_rs_finish(
+    const uint64_t *__restrict__ kin, const int32_t *__restrict__ vin, uint64_t *__restrict__ kout,
+    int32_t *__restrict__ vout, int64_t n, SortedOut so, int64_t *__restrict__ longer) {
+    __shared__ uint64_t s_k[kRsFinish + 2 * kRsRun];
+    const int64_t base = (int64_t)blockIdx.x * kRsFinish;
+    const int64_t i = base + threadIdx.x;
+    const int32_t v = i < n ? vin[i] : 0;
+    const PosMass rec = i < n ? so.xm_in[v] : PosMass{};
+    for (int t = threadIdx.x; t < kRsFinish + 2 * kRsRun; t += kRsFinish) {
+        const int64_t g = base - kRsRun + t;
+        s_k[t] = g >= 0 && g < n ? kin[g] : ~0ull;   // (no key has its top bit)
+    }
+    __syncthreads();
+    if (i >= n) return;
+    const int at = threadIdx.x + kRsRun;
+    const uint64_t key = s_k[at], top = key >> kRsTopShift;
+    int lo = 1, hi = 1;              // the nearest on either side that differ
+    while (lo <= kRsRun && s_k[at - lo] >> kRsTopShift == top) ++lo;
+    while (hi <= kRsRun && s_k[at + hi] >> kRsTopShift == top) ++hi;
+    int64_t o = i;
+    if (lo + hi - 1 > kRsRun) {
+        *longer = 1;
+    } else if (lo + hi > 2) {
+        int rank = 0;
+        for (int q = 1 - lo; q < hi; ++q) {
+            const uint64_t k = s_k[at + q];
+            rank += k < key || (k == key && q < 0);
+        }
+        o = i - (lo - 1) + rank;
+    }
+    kout[o] = key;
+    vout[o] = v;
+    so.xm[o] = rec;
+    so.gflag[o] = 0;
+    if (i == 0) so.gflag[n] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -542,14 +593,15 @@ static bool group_tiles_counted(const p3t_ctx *ctx, int64_t n) {
     return !ctx->groups_generic && (n + 1 + kScan2Tile - 1) / kScan2Tile <= kScan2MaxTiles;
 }
 
-// Root cube, keys, the kRsPasses radix passes, and the sorted particle
-// records: the first digit's histogram comes with the keys, the records with
-// the last pass.
-int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n) {
+// Root cube, keys, the radix passes, and the sorted particle records: the first
+// digit's histogram comes with the keys, the records with the last pass.  `whole`:
+// pass over all bits of the keys.
+int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n, bool whole) {
     int rc;
     const int nbb = (int)std::min<int64_t>(
         kBboxMaxBlocks, (n + (int64_t)kRedThreads * kBboxUnroll - 1) / ((int64_t)kRedThreads * kBboxUnroll));
     const int nb = (int)((n + kRsTile - 1) / kRsTile);
+    ctx->hpin[kRbSortLonger] = 0;
     if ((rc = ensure(ctx, ctx->root, sizeof(RootInfo)))) return rc;
     if ((rc = ensure(ctx, ctx->xm, n * sizeof(PosMass)))) return rc;
     if ((rc = ensure(ctx, ctx->gflag, (n + 1) * sizeof(int32_t)))) return rc;
@@ -577,12 +629,13 @@ int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n)
     int32_t *tot = ptr<int32_t>(ctx->rs_tot);
     // the input check goes straight to the pinned host words (read after the
     // topology's synchronisation)
+    const int passes = whole ? kRsPasses : kRsTopPasses, shift0 = whole ? 0 : kRsTopShift;
     k_keys_hist<<<nb, kRsThreads, 0, ctx->stream>>>(pos, mass, n, partial, nbb,
                                                      ptr<RootInfo>(ctx->root),
                                                      ctx->hpin + kRbTopoBad,
                                                      ptr<uint64_t>(ctx->keys[0]),
                                                      ptr<int32_t>(ctx->vals[0]),
-                                                     ptr<PosMass>(ctx->xm_in), cnt, nb);
+                                                     ptr<PosMass>(ctx->xm_in), shift0, cnt, nb);
     if ((rc = check_hip(ctx, hipGetLastError(), "root/keys"))) return rc;
     if (n <= kRankKeysMax) {
         k_rank_keys<<<blocks_for(n, kWave), kRankThreads, 0, ctx->stream>>>(
@@ -595,8 +648,8 @@ int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n)
     }
     const SortedOut so{ptr<PosMass>(ctx->xm_in), ptr<PosMass>(ctx->xm), ptr<int32_t>(ctx->gflag)};
     int src = 0;
-    for (int pass = 0; pass < kRsPasses; ++pass) {
-        const int shift = kRsBits * pass;
+    for (int pass = 0; pass < passes; ++pass) {
+        const int shift = shift0 + kRsBits * pass;
         uint64_t *kin = ptr<uint64_t>(ctx->keys[src]), *kout = ptr<uint64_t>(ctx->keys[1 - src]);
         int32_t *vin = ptr<int32_t>(ctx->vals[src]), *vout = ptr<int32_t>(ctx->vals[1 - src]);
         if (pass > 0) {
@@ -604,10 +657,18 @@ int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n)
             if ((rc = check_hip(ctx, hipGetLastError(), "radix hist"))) return rc;
         }
         if ((rc = scan_rows_i32(ctx, cnt, off, tot, kRsBins, nb))) return rc;
-        auto scatter = pass == kRsPasses - 1 ? k_rs_scatter<true> : k_rs_scatter<false>;
+        auto scatter = whole && pass == passes - 1 ? k_rs_scatter<true> : k_rs_scatter<false>;
         scatter<<<nb, kRsThreads, 0, ctx->stream>>>(kin, vin, kout, vout, n, shift, off, tot, nb,
                                                      so);
         if ((rc = check_hip(ctx, hipGetLastError(), "radix scatter"))) return rc;
+        src = 1 - src;
+    }
+    if (!whole) {
+        k_rs_finish<<<blocks_for(n, kRsFinish), kRsFinish, 0, ctx->stream>>>(
+            ptr<uint64_t>(ctx->keys[src]), ptr<int32_t>(ctx->vals[src]),
+            ptr<uint64_t>(ctx->keys[1 - src]), ptr<int32_t>(ctx->vals[1 - src]), n, so,
+            ctx->hpin + kRbSortLonger);
+        if ((rc = check_hip(ctx, hipGetLastError(), "radix finish"))) return rc;
         src = 1 - src;
     }
     // the passes alternate between the two buffers: an odd count ends in the second
@@ -819,7 +880,7 @@ __device__ __forceinline__ void topo_links(int64_t id, const int32_t *__restrict
     for (int k = 0; k < nc; ++k) parent[cf + k] = (int32_t)id;
 }
 
-int build_topology(p3t_ctx *ctx, int64_t n) {
+int build_topology(p3t_ctx *ctx, int64_t n, bool *unsorted) {
     int rc;
     const int nb = (int)((n + kTopoThreads - 1) / kTopoThreads);
     // n + 1: the array later holds the groups' node_at
@@ -846,6 +907,7 @@ int build_topology(p3t_ctx *ctx, int64_t n) {
     if ((rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync"))) return rc;
     if (ctx->hpin[kRbTopoBad])
         return set_error(ctx, P3T_EINVAL, "non-finite position or non-positive/non-finite mass");
+    if ((*unsorted = ctx->hpin[kRbSortLonger] != 0)) return P3T_OK;
     LevelStarts ls;
     const int32_t *hl = reinterpret_cast<const int32_t *>(ctx->hpin);
     int64_t run = 0;
