@@ -105,6 +105,28 @@ struct RowSums4 {
     }
 };
 
+// Sum (or maximum) over the wavefront of unsigned counts, in lane 63: prefix steps
+// by DPP, which reads zero past a row's edge.
+template <bool MAX>
+__device__ __forceinline__ uint64_t wave_total_u64(uint64_t v) {
+    auto step = [&](uint64_t o) { v = MAX ? (o > v ? o : v) : v + o; };
+    auto src = [&](auto ctrl, auto rows) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(
+            0, (int)(uint32_t)v, decltype(ctrl)::value, decltype(rows)::value, 0xf, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(
+            0, (int)(uint32_t)(v >> 32), decltype(ctrl)::value, decltype(rows)::value, 0xf, true);
+        return ((uint64_t)hi << 32) | lo;
+    };
+    using std::integral_constant;
+    step(src(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{}));   // row_shr:1
+    step(src(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{}));
+    step(src(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{}));
+    step(src(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{}));
+    step(src(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{}));   // row_bcast:15
+    step(src(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{}));   // row_bcast:31
+    return v;
+}
+
 template <class T>
 __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll

@@ -984,7 +984,8 @@ __device__ __forceinline__ void flush_tile_counts(const MomentArrays &A, const T
         const int lead = __builtin_ctzll(todo);
         const int32_t t = __shfl(tc.tile, lead, kWave);
         const bool same = has && tc.tile == t;
-        const int32_t sum = wave_sum(same ? tc.count : 0);
+        int32_t sum = 0;                 // counts are below 16: by bits
+        for (int b = 0; b < 4; ++b) sum += __popcll(ballot(same && tc.count >> b & 1)) << b;
         if (lane_id() == lead) atomicAdd(&A.gtile[t], sum);
         todo &= ~ballot(same);
     }
@@ -1084,6 +1085,7 @@ struct MomStage {
     int32_t count[kMomStage], first[kMomStage], n_child[kMomStage];
     uint64_t starts[kMomFlagWaves + 1];        // children that start a parent (or end the level)
     int32_t par[kMomChunk], at[kMomChunk], nc[kMomChunk];   // the chunk's parents
+    double q[kMomThreads / kMomLanes][6 * kMomChildMax];    // terms of parents in work
 };
 
 // every leaf's moments; every internal node's child count and its children's
@@ -1113,10 +1115,11 @@ __global__ __launch_bounds__(128) void k_moments_leaves(MomentArrays A, int32_t 
 // the chunk, so that every parent whose first child is in the chunk has all
 // its children on chip.  A launch is a chain of latencies, so a parent takes
 // eight lanes: each folds some components of M, S, lo, hi over the children in
-// octant order, then one of the quadrupole about the com, and stores some
-// elements of the node's records (us per level at 2^20 particles: one lane per
-// parent 9.7, sixteen 8.7, which read the children's com as often as there are
-// lanes, eight 7.0; top levels of 4096 particles: 52, 48, 38).
+// octant order, then the six quadrupole terms of one child about the com and one
+// component of their sum, and stores some elements of the node's records (us per
+// level at 2^20 particles: one lane per parent 9.7, eight with every child's
+// terms on every lane 7.0, so 6.2; top levels of 4096 particles: 52, 24, 20.
+// Handing a level to the next in LDS instead of memory gains nothing.)
 __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, int lev, int64_t cb,
                                            int64_t ce, int64_t k0) {
     const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
@@ -1170,6 +1173,7 @@ __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, 
     TileCount tc;
     const int c = t % kMomLanes, row = lane & ~(kMomLanes - 1);
     for (int p0 = 0; p0 < np; p0 += kMomThreads / kMomLanes) {
+        if (p0 + w * (kWave / kMomLanes) >= np) break;   // none for this wavefront
         const int p = p0 + t / kMomLanes;
         const bool mine = p < np;   // the same for a parent's lanes
         const int at = mine ? st.at[p] : 0, nc = mine ? st.nc[p] : 0;
@@ -1190,21 +1194,26 @@ __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, 
         const double M = __shfl(acc, row, kWave), Sx = __shfl(acc, row + 1, kWave),
                      Sy = __shfl(acc, row + 2, kWave), Sz = __shfl(acc, row + 3, kWave);
         const double cx = Sx / M, cy = Sy / M, cz = Sz / M;
-        // quadrupole component a: xx yy zz xy xz yz
-        const int a = c < 6 ? c : 0;
-        const bool diag = a < 3;
+        // the quadrupole (xx yy zz xy xz yz): each lane the six terms of one child,
+        // each of six lanes then one component over the children
+        double *const qt = st.q[t / kMomLanes];
+        {
+            const int k = at + c;
+            const double dx = st.d[kChCom][k] - cx, dy = st.d[kChCom + 1][k] - cy,
+                         dz = st.d[kChCom + 2][k] - cz;
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            const double Mk = st.d[kChM][k];
+            const double on[6] = {Mk * (3.0 * dx * dx - r2), Mk * (3.0 * dy * dy - r2),
+                                  Mk * (3.0 * dz * dz - r2), Mk * 3.0 * dx * dy,
+                                  Mk * 3.0 * dx * dz,        Mk * 3.0 * dy * dz};
+            for (int a = 0; a < 6; ++a) qt[a * kMomChildMax + c] = st.d[kChQ + a][k] + on[a];
+        }
+        wave_order();
         double q = 0.0;
-        const double *qs = st.d[kChQ + a] + at;
+        const double *qs = qt + (c < 6 ? c : 0) * kMomChildMax;
 #pragma unroll
         for (int j = 0; j < kMomChildMax; ++j) {
-            const double dx = st.d[kChCom][at + j] - cx, dy = st.d[kChCom + 1][at + j] - cy,
-                         dz = st.d[kChCom + 2][at + j] - cz;
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            const double Mk = st.d[kChM][at + j];
-            const double u = a == 0 || a == 3 || a == 4 ? dx : a == 1 || a == 5 ? dy : dz;
-            const double v = a == 3 ? dy : dz;
-            const double on = Mk * (3.0 * u * u - r2), off = Mk * 3.0 * u * v;
-            const double next = q + (qs[j] + (diag ? on : off));
+            const double next = q + qs[j];
             q = j < nc ? next : q;
         }
         if (!mine) continue;
@@ -1246,8 +1255,8 @@ __global__ __launch_bounds__(kMomThreads) void k_moments_level(MomentArrays A, i
 // The top levels top .. 0 (children levels of at most kMomTopChildren nodes, one
 // chunk) in one block; the block's barriers order each level after the one
 // below it (one compute unit: the block sees its own writes).  A level of more
-// chunks is shorter as a launch of its own (6 us) than as chunks one after the
-// other (4.5 us each).
+// chunks is shorter as a launch of its own (5.4 us) than as chunks one after the
+// other (3 us each).
 constexpr int64_t kMomTopChildren = kMomChunk;
 __global__ __launch_bounds__(kMomThreads) void k_moments_top(MomentArrays A, int top,
                                                             LevelStarts ls) {

@@ -295,6 +295,7 @@ __global__ __launch_bounds__(1024) void k_walk_stats(const GroupInfo *__restrict
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nt = (int64_t)gridDim.x * blockDim.x;
     unsigned long long tot[3] = {0, 0, 0}, mx[3] = {0, 0, 0}, pc = 0, pp = 0, ppn = 0, lv = 0;
+    int32_t first_rank = 0;   // of the thread's first group
     for (int64_t g = t0; g < G; g += nt) {
         const int ng = grp[g].count;
         const unsigned long long n = (unsigned long long)ng;
@@ -314,7 +315,8 @@ __global__ __launch_bounds__(1024) void k_walk_stats(const GroupInfo *__restrict
             atomicAdd(&s_room[b], wide ? n * (unsigned long long)cost
                                        : (unsigned long long)fp32_room(ng, c[0], c[1], c[2]));
             atomicAdd(&s_rounds[b], (unsigned long long)rounds_of(ng, wide));
-            rank[g] = (b << 24) | (int32_t)atomicAdd(&s_bin[b], 1u);
+            const int32_t r = (b << 24) | (int32_t)atomicAdd(&s_bin[b], 1u);
+            if (g == t0) first_rank = r; else rank[g] = r;
         }
     }
     __syncthreads();
@@ -328,36 +330,31 @@ __global__ __launch_bounds__(1024) void k_walk_stats(const GroupInfo *__restrict
     __syncthreads();
     if (ranks)   // this block's groups come after those already counted
         for (int64_t g = t0; g < G; g += nt) {
-            const int32_t r = rank[g];
+            const int32_t r = g == t0 ? first_rank : rank[g];
             rank[g] = r + (int32_t)s_bin[r >> 24];
         }
     for (int64_t i = t0; i < n_nodes; i += nt) lv += nchild[i] == 0;
     // wave reductions, then one set of updates per block
     __shared__ unsigned long long s_red[16][10];
     unsigned long long v[10] = {pc, pp, ppn, lv, tot[0], tot[1], tot[2], mx[0], mx[1], mx[2]};
-    for (int k = 0; k < 7; ++k) v[k] = wave_sum(v[k]);
-    for (int k = 7; k < 10; ++k)
-        for (int d = kWave / 2; d > 0; d >>= 1) {
-            const unsigned long long o = __shfl_xor(v[k], d, kWave);
-            v[k] = o > v[k] ? o : v[k];
-        }
     const int w = threadIdx.x / kWave;
-    if (lane_id() == 0)
-        for (int k = 0; k < 10; ++k) s_red[w][k] = v[k];
+    for (int k = 0; k < 10; ++k) {
+        v[k] = k < 7 ? wave_total_u64<false>(v[k]) : wave_total_u64<true>(v[k]);
+        if (lane_id() == kWave - 1) s_red[w][k] = v[k];
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 1; q < (int)(blockDim.x / kWave); ++q) {
-            for (int k = 0; k < 7; ++k) v[k] += s_red[q][k];
-            for (int k = 7; k < 10; ++k) v[k] = s_red[q][k] > v[k] ? s_red[q][k] : v[k];
+    if (threadIdx.x < 10) {
+        const int k = threadIdx.x;
+        unsigned long long r = 0;
+        for (int q = 0; q < (int)(blockDim.x / kWave); ++q) {
+            const unsigned long long x = s_red[q][k];
+            r = k < 7 ? r + x : x > r ? x : r;
         }
-        atomicAdd(&out->pc, v[0]);
-        atomicAdd(&out->pp, v[1]);
-        atomicAdd(&out->pp_near, v[2]);
-        atomicAdd(&out->n_leaves, v[3]);
-        for (int k = 0; k < 3; ++k) {
-            atomicAdd(&out->total[k], v[4 + k]);
-            atomicMax(&out->maxlen[k], v[7 + k]);
-        }
+        unsigned long long *const to[10] = {&out->pc, &out->pp, &out->pp_near, &out->n_leaves,
+                                            &out->total[0], &out->total[1], &out->total[2],
+                                            &out->maxlen[0], &out->maxlen[1], &out->maxlen[2]};
+        if (k < 7) atomicAdd(to[k], r);
+        else atomicMax(to[k], r);
     }
     if (t0 == 0) out->n_groups = (unsigned long long)G;
     // the last block hands the sums to the host's readback area
