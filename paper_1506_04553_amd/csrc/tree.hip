@@ -450,19 +450,23 @@ __global__ __launch_bounds__(kRsFinish) void k_rs_finish(
 // ---------------------------------------------------------------------------
 // Few particles: a radix pass is three launches of a few microseconds each, so
 // up to kRankMax particles one launch does it all.  Every block reduces the
-// bounding box of all particles and holds all keys in LDS; it ranks kWave
-// particles of its own, one per lane, each wavefront counting the smaller keys
-// (and equal ones of lower index) in its share of the keys, and writes their
-// sorted entries.  A wavefront counts n / 16 keys; with the launches' gaps the
-// radix passes took 110 us at 1000 particles (14 us here) and 140 at 4096 (23).
+// bounding box of all particles and holds all keys in LDS; it ranks 1 << pbits
+// particles of its own, so many that there is a block for every compute unit.
+// Each wavefront counts the smaller keys (and equal ones of lower index) in its
+// share of the keys, a particle's lanes every so-manieth of them.  With the
+// launches' gaps the radix passes took 110 us at 1000 particles and 140 at 4096;
+// this takes 11.6 and 15.8, and 21.6 at 6000 (14, 23 and 29 with 64 particles in
+// each block, whose counts then took as long as the rest).
 // ---------------------------------------------------------------------------
 constexpr int kRankThreads = 1024;
 constexpr int kRankPer = 8;                              // particles per thread
 constexpr int kRankMax = kRankThreads * kRankPer;
 constexpr int kRankWaves = kRankThreads / kWave;
+constexpr int kRankBlocks = 256;
+static_assert(kRankMax <= kRankBlocks * kWave, "particles of a block");
 
 __global__ __launch_bounds__(kRankThreads) void k_rank_sort(
-    const double *__restrict__ pos, const double *__restrict__ mass, int n,
+    const double *__restrict__ pos, const double *__restrict__ mass, int n, int pbits,
     RootInfo *__restrict__ root, int64_t *__restrict__ bad_rb, uint64_t *__restrict__ keys,
     int32_t *__restrict__ vals, PosMass *__restrict__ xm, int32_t *__restrict__ gflag) {
     __shared__ uint64_t s_key[kRankMax];
@@ -513,21 +517,24 @@ __global__ __launch_bounds__(kRankThreads) void k_rank_sort(
         if (i < n) s_key[i] = morton_key(r[k], cube.lo, cube.scale);
     }
     __syncthreads();
-    // lane's particle against the wavefront's share [b, e) of the keys: those
-    // before the block's particles count when equal, those after do not
-    const int i0 = blockIdx.x * kWave, i = i0 + lane;
+    // lane's particle against every `step`th of the wavefront's share [b, e) of the
+    // keys: those before the block's particles count when equal, those after don't
+    const int own = 1 << pbits, step = kWave >> pbits;
+    const int i0 = blockIdx.x * own, i = i0 + (lane & (own - 1));
     const uint64_t key = i < n ? s_key[i] : 0ull;
     const int per = (n + kRankWaves - 1) / kRankWaves;
     const int b = min(n, w * per), e = min(n, b + per);
-    const int e0 = min(e, max(b, i0)), e1 = min(e, max(b, i0 + kWave));
-    int cnt = 0;
+    const int e0 = min(e, max(b, i0)), e1 = min(e, max(b, i0 + own));
+    int cnt = 0, j = b + (lane >> pbits);
 #pragma unroll 8
-    for (int j = b; j < e0; ++j) cnt += s_key[j] <= key;
-    for (int j = e0; j < e1; ++j) cnt += (s_key[j] < key) | ((s_key[j] == key) & (j < i));
+    for (; j < e0; j += step) cnt += s_key[j] <= key;
+    for (; j < e1; j += step) cnt += (s_key[j] < key) | ((s_key[j] == key) & (j < i));
 #pragma unroll 8
-    for (int j = e1; j < e; ++j) cnt += s_key[j] < key;
+    for (; j < e; j += step) cnt += s_key[j] < key;
+    for (int d = own; d < kWave; d <<= 1) cnt += __shfl_xor(cnt, d, kWave);
     s_cnt[w][lane] = cnt;
     __syncthreads();
+    if (lane >= own) return;
     if (w != 0 || i >= n) return;
     int rank = 0;
     for (int k = 0; k < kRankWaves; ++k) rank += s_cnt[k][lane];
@@ -608,8 +615,10 @@ int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n,
     if (n <= kRankMax) {
         if ((rc = ensure(ctx, ctx->keys[0], n * sizeof(uint64_t)))) return rc;
         if ((rc = ensure(ctx, ctx->vals[0], n * sizeof(int32_t)))) return rc;
-        k_rank_sort<<<blocks_for(n, kWave), kRankThreads, 0, ctx->stream>>>(
-            pos, mass, (int)n, ptr<RootInfo>(ctx->root), ctx->hpin + kRbTopoBad,
+        int pbits = 2;
+        while (n > (int64_t)kRankBlocks << pbits) ++pbits;
+        k_rank_sort<<<blocks_for(n, 1 << pbits), kRankThreads, 0, ctx->stream>>>(
+            pos, mass, (int)n, pbits, ptr<RootInfo>(ctx->root), ctx->hpin + kRbTopoBad,
             ptr<uint64_t>(ctx->keys[0]), ptr<int32_t>(ctx->vals[0]), ptr<PosMass>(ctx->xm),
             ptr<int32_t>(ctx->gflag));
         return check_hip(ctx, hipGetLastError(), "rank sort");
