@@ -753,7 +753,8 @@ __global__ __launch_bounds__(kTopoThreads) void k_topo_ranges(const uint64_t *__
                                                               int32_t *__restrict__ range,
                                                               int32_t *__restrict__ blk, int nb,
                                                               int32_t *__restrict__ gtile,
-                                                              int n_gtile) {
+                                                              int n_gtile,
+                                                              int32_t *__restrict__ host) {
     __shared__ int32_t cnt[kLevels];
     __shared__ uint64_t s_k[kTopoThreads + 2 * kTopoWin];
     if (threadIdx.x < kLevels) cnt[threadIdx.x] = 0;
@@ -803,7 +804,11 @@ __global__ __launch_bounds__(kTopoThreads) void k_topo_ranges(const uint64_t *__
         for (int l = lo; l <= hi; ++l) atomicAdd(&cnt[l], 1);
     }
     __syncthreads();
-    if (threadIdx.x < kLevels) blk[(int64_t)threadIdx.x * nb + blockIdx.x] = cnt[threadIdx.x];
+    if (threadIdx.x < kLevels) {
+        const int64_t at = (int64_t)threadIdx.x * nb + blockIdx.x;
+        blk[at] = cnt[threadIdx.x];
+        if (host) host[at] = cnt[threadIdx.x];
+    }
 }
 
 // first node id of every level, and the node count at [kLevels] (computed on
@@ -812,15 +817,19 @@ struct LevelStarts {
     int64_t s[kLevels + 1];
 };
 
-// blk_off: per level, the exclusive scan of the node starts over the blocks
+// blk_off: per level, the exclusive scan of the node starts over the blocks, or
+// (`sum`) the starts themselves, of which each block then adds up those before it:
+// with at most kTopoFew blocks that is shorter than a launch for the scan, and the
+// host adds up the levels' totals
+constexpr int kTopoFew = 2 * kRbWalkWords / kLevels;   // (their room in the readback area)
 __global__ __launch_bounds__(kTopoThreads) void k_topo_emit(
     const uint64_t *__restrict__ keys, int64_t n, int n_leaf, const int32_t *__restrict__ range,
-    const int32_t *__restrict__ blk_off, const LevelStarts level_start, int nb,
+    const int32_t *__restrict__ blk_off, bool sum, const LevelStarts level_start, int nb,
     int32_t *__restrict__ level, int32_t *__restrict__ first,
     int32_t *__restrict__ count, int32_t *__restrict__ child, int32_t *__restrict__ nchild,
     uint64_t *__restrict__ prefix) {
     __shared__ uint64_t s_ball[kLevels][kTopoWaves];
-    __shared__ int32_t s_wc[kLevels][kTopoWaves];
+    __shared__ int32_t s_wc[kLevels][kTopoWaves], s_off[kLevels];
     __shared__ uint64_t s_k[kTopoThreads + kTopoWin];
     const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
     const int64_t a = (int64_t)blockIdx.x * kTopoThreads + tid;
@@ -828,6 +837,17 @@ __global__ __launch_bounds__(kTopoThreads) void k_topo_emit(
     if (win) load_key_window(s_k, keys, n, (int64_t)blockIdx.x * kTopoThreads, 0, n_leaf);
     const int32_t code = (a < n) ? range[a] : -1;
     const int lo = code < 0 ? 1 : (code & 255), hi = code < 0 ? 0 : (code >> 8);
+    if (tid < kLevels) {
+        const int32_t *row = blk_off + (int64_t)tid * nb;
+        int32_t before = 0;
+        if (sum) {
+#pragma unroll 8
+            for (int b = 0; b < (int)blockIdx.x; ++b) before += row[b];
+        } else {
+            before = row[blockIdx.x];
+        }
+        s_off[tid] = (int32_t)level_start.s[tid] + before;
+    }
     // all lanes: per-level membership masks of this wave
     for (int l = 0; l < kLevels; ++l) {
         const uint64_t b = ballot(l >= lo && l <= hi);
@@ -841,7 +861,7 @@ __global__ __launch_bounds__(kTopoThreads) void k_topo_emit(
     const uint64_t ka = win ? s_k[tid] : keys[a];
     // number of level-l starts before position a, plus the level's first id
     auto rank_at = [&](int l) -> int32_t {
-        int base = (int)level_start.s[l] + blk_off[(int64_t)l * nb + blockIdx.x];
+        int base = s_off[l];
         for (int k = 0; k < w; ++k) base += s_wc[l][k];
         return base + count_below(s_ball[l][w]);
     };
@@ -903,21 +923,29 @@ int build_topology(p3t_ctx *ctx, int64_t n, bool *unsorted) {
     const int64_t n_gtile = (n + 1 + kScan2Tile - 1) / kScan2Tile;
     const bool gcount = group_tiles_counted(ctx, n);
     if (gcount && (rc = ensure(ctx, ctx->gtile, n_gtile * sizeof(int32_t)))) return rc;
+    const bool few = nb <= kTopoFew;
+    int32_t *starts = reinterpret_cast<int32_t *>(ctx->hpin + kRbWalk);   // (few)
     k_topo_ranges<<<nb, kTopoThreads, 0, ctx->stream>>>(
         keys, n, ctx->prm.n_leaf, ptr<int32_t>(ctx->lvlrange), blk, nb,
-        gcount ? ptr<int32_t>(ctx->gtile) : nullptr, gcount ? (int)n_gtile : 0);
+        gcount ? ptr<int32_t>(ctx->gtile) : nullptr, gcount ? (int)n_gtile : 0,
+        few ? starts : nullptr);
     if ((rc = check_hip(ctx, hipGetLastError(), "topology ranges"))) return rc;
     // the per-level node counts (int32, in the words before the input check) go
     // straight to the pinned host words; one synchronisation makes them and the
     // input check visible
     static_assert(kLevels * sizeof(int32_t) <= kRbTopoBad * sizeof(int64_t), "readback layout");
     int32_t *level_total = reinterpret_cast<int32_t *>(ctx->hpin);
-    if ((rc = scan_rows_i32(ctx, blk, blk_off, level_total, kLevels, nb))) return rc;
+    if (!few && (rc = scan_rows_i32(ctx, blk, blk_off, level_total, kLevels, nb))) return rc;
     if ((rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync"))) return rc;
     if (ctx->hpin[kRbTopoBad])
         return set_error(ctx, P3T_EINVAL, "non-finite position or non-positive/non-finite mass");
     if ((*unsorted = ctx->hpin[kRbSortLonger] != 0)) return P3T_OK;
     LevelStarts ls;
+    if (few)
+        for (int l = 0; l < kLevels; ++l) {
+            level_total[l] = 0;
+            for (int b = 0; b < nb; ++b) level_total[l] += starts[l * nb + b];
+        }
     const int32_t *hl = reinterpret_cast<const int32_t *>(ctx->hpin);
     int64_t run = 0;
     for (int l = 0; l < kLevels; ++l) {
@@ -935,7 +963,8 @@ int build_topology(p3t_ctx *ctx, int64_t n, bool *unsorted) {
         if ((rc = ensure(ctx, *b, nn * sizeof(int32_t)))) return rc;
     if ((rc = ensure(ctx, ctx->node_prefix, nn * sizeof(uint64_t)))) return rc;
     k_topo_emit<<<nb, kTopoThreads, 0, ctx->stream>>>(
-        keys, n, ctx->prm.n_leaf, ptr<int32_t>(ctx->lvlrange), blk_off, ls, nb, ptr<int32_t>(ctx->node_level),
+        keys, n, ctx->prm.n_leaf, ptr<int32_t>(ctx->lvlrange), few ? blk : blk_off, few, ls, nb,
+        ptr<int32_t>(ctx->node_level),
         ptr<int32_t>(ctx->node_first), ptr<int32_t>(ctx->node_count), ptr<int32_t>(ctx->node_child),
         ptr<int32_t>(ctx->node_nchild), ptr<uint64_t>(ctx->node_prefix));
     return check_hip(ctx, hipGetLastError(), "topology emit");
