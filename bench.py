@@ -71,8 +71,9 @@ F_VJP_PC = 190
 BUILD_BYTES_PER_PARTICLE = {
     "bbox": 24,                      # read positions
     "keys": 24 + 12,                 # read positions; write key + index
-    "sort": 8 * (8 + 12 + 12),       # 8 passes: histogram reads the key, scatter
-                                     # reads and writes key + index
+    "sort": 5 * (8 + 12 + 12) + 20,  # 5 passes: histogram reads the key, scatter
+                                     # reads and writes key + index; the last step
+                                     # reads and writes the key, writes the index
     "gather": 4 + 32 + 32,           # read index, position + mass; write x y z m
     "topology": 16,                  # sorted keys read by the neighbour comparisons
     "moments": 64,                   # leaves read x y z m twice
