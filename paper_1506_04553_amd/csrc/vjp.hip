@@ -26,10 +26,10 @@
 // member's cell and far-particle terms are summed in R over the 64 entries of
 // a wavefront (a fixed tree) before joining an FP64 sum.
 //
-// Two passes over each group's lists: the first sums the near-particle terms
-// of each member; the second sums, for each list entry, the terms of all
-// members and scatters them, and evaluates each (member, cell) and (member,
-// far particle) term only once, for both sides.
+// Two passes over each group's lists: the first (mixed precision only) sums the
+// near-particle terms of each member; the second sums, for each list entry, the
+// terms of all members and scatters them, and evaluates each (member, cell) and
+// (member, far particle) term, in FP64 also each near one, only once, for both sides.
 //
 // The pair and cell terms are evaluated in the precision of the forward pass
 // (R = double, or R = float on offsets from the group's centre taken in FP64,
@@ -47,6 +47,8 @@
 // own adds made 39.8 million and took 2.93; without any adds it takes 1.83.
 // The push-down of the cell adjoints is FP64.
 #include <math.h>
+
+#include <type_traits>
 
 #include "device_util.h"
 #include "internal.h"
@@ -270,6 +272,14 @@ __device__ __forceinline__ VjpCell<R> stage_cell(const NodeMP &c, const double s
 constexpr int kFold = 32;
 // a run of member terms is parked one lane per member and row, 16 members at a time
 static_assert(kFold % 16 == 0, "whole runs");
+
+// Whether the second pass gives the members their near-particle terms too, as it
+// does for far particles and cells.  In FP64 the first pass is then left out
+// (forward and backward of 15001 particles 542 -> 520 us, the backward of 262144
+// 3.82 -> 3.72 ms).  In FP32 it stays: these are a member's largest terms, summed in
+// runs of the member's own before they join an FP64 sum.
+template <class R>
+constexpr bool kNearBoth = sizeof(R) == 8;
 
 // a list particle as staged in LDS: position (shifted) and mass
 template <class R>
@@ -518,55 +528,67 @@ __global__ __launch_bounds__(kVjpThreads, sizeof(R) == 4 && !CELL_K ? 4 : 2) voi
         }
         __syncthreads();
         for (int k = lane; k < nc; k += kWave) s_gr[w][k][0] = s_gr[w][k][1] = s_gr[w][k][2] = 0.0;
-        // far particles (K = W = 1, never a member): a lane per entry, the
-        // members from LDS; each pair's term counts for both sides, the
-        // members' parts gathered as for the cells below.  Lanes past the end
-        // hold a massless particle far away, whose terms are exactly zero.
-        for (int64_t e0 = (int64_t)w * kWave; e0 < nf; e0 += kVjpThreads) {
-            const bool valid = e0 + lane < nf;
-            const int32_t j = valid ? p_idx[fb + e0 + lane] : 0;
-            const PosMass pj = xm[j];
-            const R xj = valid ? (R)(pj.x - sh[0]) : R(1e18), yj = valid ? (R)(pj.y - sh[1]) : R(1e18),
-                    zj = valid ? (R)(pj.z - sh[2]) : R(1e18);
-            const R mj = valid ? (R)pj.m : R(0);
-            double acc[4] = {0, 0, 0, 0};
-            for (int k0 = 0; k0 < nc; k0 += kFold) {
-                const int k1 = min(nc, k0 + kFold);
-                R p[4] = {0, 0, 0, 0};
-#pragma unroll 1
-                for (int r0 = k0; r0 < k1; r0 += 16) {
-                    R mg[3] = {0, 0, 0};
-                    row_runs(r0, k1, lane, mg, [&](int k, R gd[3]) {
-                        const VjpMember<R> q = s_i[k];
-                        R gmj;
-                        pair_grad<R, false>(xj - q.x, yj - q.y, zj - q.z, mj, q.wx, q.wy, q.wz, q.c,
-                                            vp, gd, gmj);
-                        p[0] += gd[0]; p[1] += gd[1]; p[2] += gd[2]; p[3] += gmj;
-                    });
-                    const int k = r0 + row_member(lane);
-                    for (int a = 0; a < 3; ++a) {
-                        mg[a] += __shfl_xor(mg[a], 16, kWave);
-                        mg[a] += __shfl_xor(mg[a], 32, kWave);
-                        if (lane < 16 && k < k1) s_gr[w][k][a] -= (double)mg[a];   // -dl/dd
-                    }
-                }
-                for (int a = 0; a < 4; ++a) acc[a] += (double)p[a];
-            }
-            scatter_add<4>(s_out[w], acc, valid ? j : -1, lane, padj);
-        }
-        // near particles (the list may hold a member): a lane per entry, this
-        // side only
-        for (int64_t e0 = nf + (int64_t)w * kWave; e0 < np; e0 += kVjpThreads) {
-            const bool valid = e0 + lane < np;
-            int32_t j = -1;
-            double acc[4] = {0, 0, 0, 0};
-            if (valid) {
-                j = n_idx[nb + (e0 + lane - nf)];
+        // particles: a lane per entry, the members from LDS; each pair's term
+        // counts for both sides, the members' parts gathered as for the cells
+        // below.  Far ones have K = W = 1 and are never a member; a near one may
+        // be, and adds nothing to itself.  Lanes past the end hold a massless
+        // particle far away, whose terms are exactly zero.
+        auto particles = [&](auto near, const int32_t *__restrict__ idx, int64_t count) {
+            constexpr bool NEAR = decltype(near)::value;
+            for (int64_t e0 = (int64_t)w * kWave; e0 < count; e0 += kVjpThreads) {
+                const bool valid = e0 + lane < count;
+                const int32_t j = valid ? idx[e0 + lane] : 0;
                 const PosMass pj = xm[j];
-                const R xj = (R)(pj.x - sh[0]), yj = (R)(pj.y - sh[1]), zj = (R)(pj.z - sh[2]);
-                vjp_scatter_pp<R, true>(s_i, s_id, nc, j, xj, yj, zj, (R)pj.m, vp, acc);
+                const R xj = valid ? (R)(pj.x - sh[0]) : R(1e18),
+                        yj = valid ? (R)(pj.y - sh[1]) : R(1e18),
+                        zj = valid ? (R)(pj.z - sh[2]) : R(1e18);
+                const R mj = valid ? (R)pj.m : R(0);
+                double acc[4] = {0, 0, 0, 0};
+                for (int k0 = 0; k0 < nc; k0 += kFold) {
+                    const int k1 = min(nc, k0 + kFold);
+                    R p[4] = {0, 0, 0, 0};
+#pragma unroll 1
+                    for (int r0 = k0; r0 < k1; r0 += 16) {
+                        R mg[3] = {0, 0, 0};
+                        row_runs(r0, k1, lane, mg, [&](int k, R gd[3]) {
+                            const VjpMember<R> q = s_i[k];
+                            R gmj = R(0);
+                            if (NEAR && valid && s_id[k] == j)
+                                gd[0] = gd[1] = gd[2] = R(0);
+                            else
+                                pair_grad<R, NEAR>(xj - q.x, yj - q.y, zj - q.z, mj, q.wx, q.wy,
+                                                   q.wz, q.c, vp, gd, gmj);
+                            p[0] += gd[0]; p[1] += gd[1]; p[2] += gd[2]; p[3] += gmj;
+                        });
+                        const int k = r0 + row_member(lane);
+                        for (int a = 0; a < 3; ++a) {
+                            mg[a] += __shfl_xor(mg[a], 16, kWave);
+                            mg[a] += __shfl_xor(mg[a], 32, kWave);
+                            if (lane < 16 && k < k1) s_gr[w][k][a] -= (double)mg[a];   // -dl/dd
+                        }
+                    }
+                    for (int a = 0; a < 4; ++a) acc[a] += (double)p[a];
+                }
+                scatter_add<4>(s_out[w], acc, valid ? j : -1, lane, padj);
             }
-            scatter_add<4>(s_out[w], acc, j, lane, padj);
+        };
+        particles(std::false_type(), p_idx + fb, nf);
+        if constexpr (kNearBoth<R>) {
+            particles(std::true_type(), n_idx + nb, np - nf);
+        } else {
+            // near particles: this side only
+            for (int64_t e0 = nf + (int64_t)w * kWave; e0 < np; e0 += kVjpThreads) {
+                const bool valid = e0 + lane < np;
+                int32_t j = -1;
+                double acc[4] = {0, 0, 0, 0};
+                if (valid) {
+                    j = n_idx[nb + (e0 + lane - nf)];
+                    const PosMass pj = xm[j];
+                    const R xj = (R)(pj.x - sh[0]), yj = (R)(pj.y - sh[1]), zj = (R)(pj.z - sh[2]);
+                    vjp_scatter_pp<R, true>(s_i, s_id, nc, j, xj, yj, zj, (R)pj.m, vp, acc);
+                }
+                scatter_add<4>(s_out[w], acc, j, lane, padj);
+            }
         }
         // cells: a lane per entry, the members from LDS.  Each pair's dl/dr
         // counts for both sides: the cell's sums stay in the lane; the
@@ -729,9 +751,10 @@ __global__ void k_vjp_unpermute(int64_t n, const int32_t *__restrict__ perm,
     gmass[o] = padj[4 * s + 3];
 }
 
-__global__ void k_vjp_zero(int64_t count, double *__restrict__ a) {
+__global__ void k_vjp_zero(int64_t na, double *__restrict__ a, int64_t nb, double *__restrict__ b) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < count) a[k] = 0.0;
+    if (k < na) a[k] = 0.0;
+    else if (k < na + nb) b[k - na] = 0.0;
 }
 
 int launch_vjp(p3t_ctx *ctx, const double *w, const double *c, double *gpos, double *gmass) {
@@ -760,10 +783,13 @@ int launch_vjp_ws(p3t_ctx *ctx, const double *w, const double *c, double *gpos, 
     vp.use_quad = ctx->prm.use_quadrupole ? 1 : 0;
     vp.has_c = c != nullptr;
     const ListsDev L = lists_dev(ctx);
-    // the cell adjoints are accumulated: clear them (a fill kernel, which a
-    // caller's graph capture records as an ordinary kernel node)
+    // the cell adjoints are accumulated, and so are the particles' where the first
+    // pass does not set them: clear them (a fill kernel, which a caller's graph
+    // capture records as an ordinary kernel node)
+    const bool mixed = ctx->prm.precision == P3T_PREC_MIXED;
     const int64_t words = cell_adj(vp.use_quad) * nn;
-    k_vjp_zero<<<blocks_for(words, 256), 256, 0, ctx->stream>>>(words, cadj);
+    const int64_t pwords = (mixed ? kNearBoth<float> : kNearBoth<double>) ? 4 * n : 0;
+    k_vjp_zero<<<blocks_for(words + pwords, 256), 256, 0, ctx->stream>>>(words, cadj, pwords, padj);
     if ((rc = check_hip(ctx, hipGetLastError(), "vjp clear"))) return rc;
     // a group that the interaction kernel splits is shared by as many blocks here
     const unsigned blocks = (unsigned)work_blocks(ctx);
@@ -771,8 +797,6 @@ int launch_vjp_ws(p3t_ctx *ctx, const double *w, const double *c, double *gpos, 
     // accepted cells lie at least h from every member: K = W = 1 on them when h >= r_out
     const bool cell_k = ctx->prm.r_search < ctx->prm.r_out;
     // the adjoint terms follow the forward pass's precision
-    const bool mixed = ctx->prm.precision == P3T_PREC_MIXED;
-    auto ki = mixed ? k_vjp_i<float> : k_vjp_i<double>;
     const bool quad = vp.use_quad != 0;
     auto ks = mixed ? (cell_k ? (quad ? k_vjp_scatter<float, true, true>
                                       : k_vjp_scatter<float, true, false>)
@@ -782,9 +806,10 @@ int launch_vjp_ws(p3t_ctx *ctx, const double *w, const double *c, double *gpos, 
                                       : k_vjp_scatter<double, true, false>)
                               : (quad ? k_vjp_scatter<double, false, true>
                                       : k_vjp_scatter<double, false, false>));
-    ki<<<blocks, kVjpThreads, 0, ctx->stream>>>(ptr<GroupInfo>(ctx->grp), L, wd,
-                                                ptr<PosMass>(ctx->xm), ptr<int32_t>(ctx->vals[0]),
-                                                w, c, vp, padj);
+    if (!pwords)
+        k_vjp_i<float><<<blocks, kVjpThreads, 0, ctx->stream>>>(
+            ptr<GroupInfo>(ctx->grp), L, wd, ptr<PosMass>(ctx->xm), ptr<int32_t>(ctx->vals[0]), w, c,
+            vp, padj);
     if ((rc = check_hip(ctx, hipGetLastError(), "vjp i-side"))) return rc;
     ks<<<blocks, kVjpThreads, 0, ctx->stream>>>(
         ptr<GroupInfo>(ctx->grp), L, wd, ptr<PosMass>(ctx->xm), ptr<NodeMP>(ctx->node_mp),
