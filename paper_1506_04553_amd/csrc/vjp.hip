@@ -17,8 +17,8 @@
 // contribution is the quadratic form f(x) = d^T B d + beta.d + gamma with
 // B = 3 S - tr(S) I, beta = dl/dcom / M, gamma = dl/dM, and
 //   dL/dm_k += f(x_k),   dL/dx_k += m_k (2 B d_k + beta).
-// The forms of a leaf's ancestors are summed top-down, each re-centred at the
-// child's centre of mass, so every particle needs only its leaf's form.
+// The forms of a leaf and its ancestors are summed, each re-centred at the leaf's
+// centre of mass, so every particle needs only its leaf's form.
 //
 // The adjoint arithmetic takes no decisions (the lists are frozen), so unlike
 // the rest of the library it lets the compiler fuse multiply-adds.  Runs of at
@@ -665,8 +665,8 @@ __global__ __launch_bounds__(kVjpThreads, sizeof(R) == 4 && !CELL_K ? 4 : 2) voi
 }
 
 // ---------------------------------------------------------------------------
-// Pass 3: per leaf, sum the quadratic forms of its ancestors (re-centred at
-// each child's centre of mass) and apply them to the leaf's members.
+// Pass 3: per leaf, sum the quadratic forms of its ancestors (re-centred at the
+// leaf's centre of mass) and apply them to the leaf's members.
 // ---------------------------------------------------------------------------
 struct Form {
     double B[6];     // symmetric xx yy zz xy xz yz
@@ -706,49 +706,57 @@ __device__ __forceinline__ void form_shift(Form &f, const double e[3]) {
     for (int a = 0; a < 3; ++a) f.b[a] += 2.0 * Be[a];
 }
 
-__global__ void k_vjp_down(int64_t n_nodes, const int32_t *__restrict__ nchild,
-                           const int32_t *__restrict__ parent, const NodeMP *__restrict__ mp,
-                           const NodeWalk *__restrict__ nw, const double *__restrict__ cadj,
-                           bool quad, const PosMass *__restrict__ xm,
-                           double *__restrict__ padj) {
-    const int64_t leaf = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Latency bounds it: the chain of parents, then the loads of the ancestors' forms
+// and of the members.  A leaf has eight lanes: each takes every eighth ancestor,
+// whose form is re-centred at the leaf's centre of mass at once, and every eighth
+// member, which it hands over in the caller's order.  15001 particles: 10.4 us; with
+// a lane per leaf, the forms taken down the chain level by level, and a launch of its
+// own for the caller's order 22.5 (262144: 32 and 35).
+constexpr int kDownLanes = 8;
+constexpr int kDownThreads = 256;
+__global__ __launch_bounds__(kDownThreads) void k_vjp_down(
+    int64_t n_nodes, const int32_t *__restrict__ nchild, const int32_t *__restrict__ parent,
+    const NodeMP *__restrict__ mp, const NodeWalk *__restrict__ nw,
+    const double *__restrict__ cadj, bool quad, const PosMass *__restrict__ xm,
+    const int32_t *__restrict__ perm, const double *__restrict__ padj, double *__restrict__ gpos,
+    double *__restrict__ gmass) {
+    const int64_t leaf = ((int64_t)blockIdx.x * kDownThreads + threadIdx.x) / kDownLanes;
+    const int sub = threadIdx.x % kDownLanes;
     if (leaf >= n_nodes || nchild[leaf] != 0) return;
-    int32_t chain[kLevels + 1];
-    int depth = 0;
-    for (int32_t c = (int32_t)leaf; c >= 0 && depth <= kLevels; c = parent[c]) chain[depth++] = c;
-    Form f{};
-    for (int k = depth - 1; k >= 0; --k) {
-        const int32_t c = chain[k];
-        if (k < depth - 1) {
-            const int32_t p = chain[k + 1];
-            const double e[3] = {mp[c].cx - mp[p].cx, mp[c].cy - mp[p].cy, mp[c].cz - mp[p].cz};
-            form_shift(f, e);
-        }
-        form_add_own(f, cadj + (int64_t)c * cell_adj(quad), quad, mp[c].M);
-    }
     const double cx = mp[leaf].cx, cy = mp[leaf].cy, cz = mp[leaf].cz;
     const int32_t first = nw[leaf].first, cnt = nw[leaf].count;
-    for (int32_t k = first; k < first + cnt; ++k) {
+    Form f{};
+    int depth = 0;
+    for (int32_t c = (int32_t)leaf; c >= 0 && depth <= kLevels; c = parent[c], ++depth) {
+        if (depth % kDownLanes != sub) continue;
+        const NodeMP &m = mp[c];
+        const double e[3] = {cx - m.cx, cy - m.cy, cz - m.cz};
+        Form own{};
+        form_add_own(own, cadj + (int64_t)c * cell_adj(quad), quad, m.M);
+        form_shift(own, e);
+        for (int a = 0; a < 6; ++a) f.B[a] += own.B[a];
+        for (int a = 0; a < 3; ++a) f.b[a] += own.b[a];
+        f.g += own.g;
+    }
+    auto total = [](double &v) {   // over the eight lanes: xor 1, xor 2, then the mirror
+        v += dpp_src<0xB1>(v);
+        v += dpp_src<0x4E>(v);
+        v += dpp_src<0x141>(v);
+    };
+    for (int a = 0; a < 6; ++a) total(f.B[a]);
+    for (int a = 0; a < 3; ++a) total(f.b[a]);
+    total(f.g);
+    for (int32_t k = first + sub; k < first + cnt; k += kDownLanes) {
         const PosMass pk = xm[k];
+        const int64_t o = perm[k];
+        const double *const p = padj + 4 * (int64_t)k;
         const double d[3] = {pk.x - cx, pk.y - cy, pk.z - cz};
         double Bd[3];
         Bmul(f.B, d, Bd);
-        double *p = padj + 4 * (int64_t)k;
-        p[3] += d[0] * Bd[0] + d[1] * Bd[1] + d[2] * Bd[2] + f.b[0] * d[0] + f.b[1] * d[1] +
-                f.b[2] * d[2] + f.g;
-        const double mk = pk.m;
-        for (int a = 0; a < 3; ++a) p[a] += mk * (2.0 * Bd[a] + f.b[a]);
+        gmass[o] = p[3] + (d[0] * Bd[0] + d[1] * Bd[1] + d[2] * Bd[2] + f.b[0] * d[0] +
+                           f.b[1] * d[1] + f.b[2] * d[2] + f.g);
+        for (int a = 0; a < 3; ++a) gpos[3 * o + a] = p[a] + pk.m * (2.0 * Bd[a] + f.b[a]);
     }
-}
-
-__global__ void k_vjp_unpermute(int64_t n, const int32_t *__restrict__ perm,
-                                const double *__restrict__ padj, double *__restrict__ gpos,
-                                double *__restrict__ gmass) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    const int64_t o = perm[s];
-    for (int a = 0; a < 3; ++a) gpos[3 * o + a] = padj[4 * s + a];
-    gmass[o] = padj[4 * s + 3];
 }
 
 __global__ void k_vjp_zero(int64_t na, double *__restrict__ a, int64_t nb, double *__restrict__ b) {
@@ -815,13 +823,11 @@ int launch_vjp_ws(p3t_ctx *ctx, const double *w, const double *c, double *gpos, 
         ptr<GroupInfo>(ctx->grp), L, wd, ptr<PosMass>(ctx->xm), ptr<NodeMP>(ctx->node_mp),
         ptr<int32_t>(ctx->vals[0]), w, c, vp, padj, cadj);
     if ((rc = check_hip(ctx, hipGetLastError(), "vjp scatter"))) return rc;
-    k_vjp_down<<<blocks_for(nn, 128), 128, 0, ctx->stream>>>(
+    k_vjp_down<<<blocks_for(nn * kDownLanes, kDownThreads), kDownThreads, 0, ctx->stream>>>(
         nn, ptr<int32_t>(ctx->node_nchild), ptr<int32_t>(ctx->node_parent), ptr<NodeMP>(ctx->node_mp),
-        ptr<NodeWalk>(ctx->node_walk), cadj, quad, ptr<PosMass>(ctx->xm), padj);
-    if ((rc = check_hip(ctx, hipGetLastError(), "vjp push-down"))) return rc;
-    k_vjp_unpermute<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(n, ptr<int32_t>(ctx->vals[0]), padj,
-                                                                 gpos, gmass);
-    return check_hip(ctx, hipGetLastError(), "vjp unpermute");
+        ptr<NodeWalk>(ctx->node_walk), cadj, quad, ptr<PosMass>(ctx->xm), ptr<int32_t>(ctx->vals[0]),
+        padj, gpos, gmass);
+    return check_hip(ctx, hipGetLastError(), "vjp push-down");
 }
 
 }  // namespace p3t
