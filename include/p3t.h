@@ -320,7 +320,10 @@ int p3t_step(p3t_ctx *ctx, int64_t n, double *pos, double *vel, const double *ma
  * (Section 2.1: F_soft and F_hard, H_soft and H_hard; d = x_j - x_i, s the
  * softened distance).  O(n^2) work; uses eps, r_in, r_out of *p.
  *   pos device [n][3]; mass device [n]; acc device [n][3] out; pot device [n]
- *   out or NULL.  Errors: EINVAL, EHIP. */
+ *   out or NULL.  The context keeps a workspace of 256 MiB (64 n bytes beyond four
+ *   million particles) for it; without memory for that, and under stream capture,
+ *   the call takes none and evaluates every pair from both sides.  Errors: EINVAL,
+ *   EHIP. */
 #define P3T_DIRECT_NEWTON 0
 #define P3T_DIRECT_SOFT 1
 #define P3T_DIRECT_HARD 2
