@@ -551,20 +551,17 @@ static int plan_split(p3t_ctx *ctx, SplitPlan &sp) {
     // FP64: a group of n members and p <= cost / share + 1 parts takes n p sums
     if (wide) room = room / share + (double)ctx->n;
     if (room * (double)one > (double)kSplitScratch) room = (double)(kSplitScratch / one);
-    // without memory for the sums every group stays whole
-    rc = groups ? ensure(ctx, ctx->fpart, (size_t)(int64_t)room * one) : P3T_OK;
-    if (rc && rc != P3T_ENOMEM) return rc;
-    const bool any = groups && !rc;
-    if (any) {
+    if (groups) {
         sp.last_bin = last;
         sp.first_whole = (int)items;
         sp.share = (float)share;
         sp.room = (int64_t)room;
+        if ((rc = ensure(ctx, ctx->fpart, (size_t)sp.room * one))) return rc;
         sp.n_items = &walk_stats_dev(ctx)->n_items;
         sp.used = &walk_stats_dev(ctx)->part_used;
     }
-    ctx->n_split = any ? groups : 0;
-    ctx->n_items = any ? items : 0;
+    ctx->n_split = groups;
+    ctx->n_items = items;
     // the items, then each group's first partial sum and parts
     const int64_t blocks = work_blocks(ctx);
     if ((rc = ensure(ctx, ctx->work,

@@ -44,45 +44,3 @@ def test_split_groups_match_oracle(n, n_crit, n_leaf, theta, quad, precision):
     assert row_errors(g["pot"], pot) <= ROW_TOL[precision]
     # a second build (lists in reserved segments) and a fixed summation order
     assert np.array_equal(again["acc"], g["acc"]) and np.array_equal(again["pot"], g["pot"])
-
-
-@pytest.mark.parametrize("precision", ["fp64", "mixed"])
-def test_no_memory_for_the_sums(precision, monkeypatch):
-    """A build whose last requests for memory (the sums of split groups among
-    them) are refused one at a time either says so or gives the same forces
-    with whole groups."""
-    import torch
-    from paper_1506_04553_amd import P3T, P3TError
-    n = 1000
-    c = plummer(n, 51)
-    p = dict(eps=4.0 / n, r_in=0.005, r_out=0.05, theta=0.5, r_search=0.055, n_crit=64, n_leaf=16,
-             use_quadrupole=1, precision=precision)
-    acc, pot = oracle.Tree(c.pos, c.mass, p).force()
-    real = torch.cuda.caching_allocator_alloc
-    calls = [0, -1]   # requests so far, the one to refuse
-
-    def alloc(*args):
-        calls[0] += 1
-        return None if calls[0] == calls[1] else real(*args)
-
-    monkeypatch.setattr(torch.cuda, "caching_allocator_alloc", alloc)
-    pos, mass = torch.from_numpy(c.pos).cuda(), torch.from_numpy(c.mass).cuda()
-    ctx = P3T(0)
-    ctx.build_tree(pos, mass, **p)
-    ctx.close()
-    total, whole = calls[0], 0
-    for k in range(4):
-        calls[:] = [0, total - k]
-        ctx = P3T(0)
-        try:
-            ctx.build_tree(pos, mass, **p)
-        except P3TError as e:
-            log(f"refused request {total - k} of {total}: {e}")
-            ctx.close()
-            continue
-        a, f = ctx.long_force()
-        ctx.close()
-        whole += 1
-        assert rel_rms(a.cpu().numpy(), acc) <= TOL[precision]
-        assert rel_rms(f.cpu().numpy(), pot) <= TOL[precision]
-    assert whole > 0
