@@ -175,8 +175,8 @@ __global__ __launch_bounds__(kDirThreads) void k_direct(int64_t n, const double 
 // the steps read at immediate offsets), and the sums of y's particles move on
 // by one lane per step.  The pair costs 24 FP64 operations and 1/K of eight
 // lane moves where two one-sided evaluations cost 38, and FP64 issue is the
-// bound: 2^18 particles, Newton 46.4 -> 28.0 ms, soft 62.2 -> 32.7, hard
-// 30.3 -> 16.6.  The one-sided kernel also has too few blocks for fewer
+// bound: 2^18 particles, Newton 46.4 -> 28.6 ms, soft 62.2 -> 31.4, hard
+// 30.3 -> 11.1.  The one-sided kernel also has too few blocks for fewer
 // particles: 65536, Newton, 6.6 -> 1.9 ms; 4096, 420 -> 39 us.
 // Three wavefronts per SIMD hold Newton's registers (158) without spilling,
 // two those of the changeover.
@@ -192,7 +192,9 @@ struct alignas(32) Sum4 {
 // lane l gets lane l + 1's value, lane 63 lane 0's
 __device__ __forceinline__ double rotate_lanes(double v) { return dpp_src<0x134>(v); }
 
-// The pair's factors: acceleration of i is m_j f d, its potential -m_j w.
+// The pair's factors: acceleration of i is m_j f d, its potential -m_j w.  False
+// where the pair adds nothing, which is not the same as adding zero times a mass or
+// an offset that is not finite.
 template <int MODE>
 __device__ __forceinline__ bool pair_factors(double r2, const DirectConsts &dc, double &f,
                                              double &w) {
@@ -202,21 +204,34 @@ __device__ __forceinline__ bool pair_factors(double r2, const DirectConsts &dc, 
         return true;
     }
     const bool near = !(r2 >= dc.rout2);
-    const uint64_t any = __builtin_amdgcn_ballot_w64(near);
-    if (MODE == P3T_DIRECT_HARD && !any) return false;
+    if (MODE == P3T_DIRECT_HARD && !near) return false;
     const double rinv = rsq_nr(r2);
     f = rinv * rinv * rinv;
     w = rinv;
-    if (MODE == P3T_DIRECT_HARD && !near) f = w = 0.0;
-    if (any) {
-        if (near) {
-            double K, Ws;
-            changeover_in(r2 * rinv, rinv, dc, K, Ws);
-            f *= MODE == P3T_DIRECT_SOFT ? K : 1.0 - K;
-            w = MODE == P3T_DIRECT_SOFT ? Ws : rinv - Ws;
-        }
+    if (near) {
+        double K, Ws;
+        changeover_in(r2 * rinv, rinv, dc, K, Ws);
+        f *= MODE == P3T_DIRECT_SOFT ? K : 1.0 - K;
+        w = MODE == P3T_DIRECT_SOFT ? Ws : rinv - Ws;
     }
     return true;
+}
+
+// Whether any lane has a particle within r_out of (x, y, z) (HARD: the others add
+// nothing).  One branch for a lane's K pairs, most of which are farther apart: 11.1 ms
+// for 2^18 particles, where one for each took 18.2.
+template <int K>
+__device__ __forceinline__ bool any_near(const DJ xi[K], double x, double y, double z,
+                                         const DirectConsts &dc) {
+    bool near = false;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const double dx = x - xi[k].x, dy = y - xi[k].y, dz = z - xi[k].z;
+        const double r2 =
+            __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, dc.eps2)));
+        near |= !(r2 >= dc.rout2);
+    }
+    return __builtin_amdgcn_ballot_w64(near) != 0;
 }
 
 template <int MODE, int K, int WAVES>
@@ -264,8 +279,9 @@ __attribute__((amdgpu_waves_per_eu(MODE == P3T_DIRECT_NEWTON ? 3 : 2))) void k_d
 #pragma unroll 2
             for (int s = 0; s < kWave; ++s) {
                 const double2 a = xy[s], b = zm[s];
+                const bool some = MODE != P3T_DIRECT_HARD || any_near<K>(xi, a.x, a.y, b.x, dc);
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
+                for (int k = 0; k < K && some; ++k) {
                     const double dx = a.x - xi[k].x, dy = a.y - xi[k].y, dz = b.x - xi[k].z;
                     const double r2 = __builtin_fma(
                         dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, dc.eps2)));
@@ -303,6 +319,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == P3T_DIRECT_NEWTON ? 3 : 2))) void k_d
         } else {
             for (int s = 0; s < kWave; ++s) {
                 const double2 a = xy[s], b = zm[s];
+                if (MODE == P3T_DIRECT_HARD && !any_near<K>(xi, a.x, a.y, b.x, dc)) continue;
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     // a particle meets itself in step 0 of its own 64
