@@ -16,6 +16,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device_util.h"
 #include "internal.h"
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(kDirThreads) void k_direct(int64_t n, const double 
 // by one lane per step.  The pair costs 24 FP64 operations and 1/K of eight
 // lane moves where two one-sided evaluations cost 38, and FP64 issue is the
 // bound: 2^18 particles, Newton 46.4 -> 28.6 ms, soft 62.2 -> 31.4, hard
-// 30.3 -> 11.1.  The one-sided kernel also has too few blocks for fewer
+// 30.3 -> 11.5.  The one-sided kernel also has too few blocks for fewer
 // particles: 65536, Newton, 6.6 -> 1.9 ms; 4096, 420 -> 39 us.
 // Three wavefronts per SIMD hold Newton's registers (158) without spilling,
 // two those of the changeover.
@@ -251,10 +252,12 @@ __attribute__((amdgpu_waves_per_eu(MODE == P3T_DIRECT_NEWTON ? 3 : 2))) void k_d
     Sum4 *const row_x = rows + (int64_t)(2 * blockIdx.y) * np + (int64_t)x * B;
     Sum4 *const row_y = rows + (int64_t)(2 * blockIdx.y + 1) * np + (int64_t)y * B;
 
-    // padding particles are massless and far away: their terms are zero
+    // Padding particles are massless and lie where the last particle does: wherever the
+    // others are, they are as far from them as that one, and their terms are zero.
+    // (It meets them in its own block alone, which leaves them out.)
     auto load = [&](int64_t i) {
-        return i < n ? DJ{pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], mass[i]}
-                     : DJ{1e18, 1e18, 1e18, 0.0};
+        const int64_t p = i < n ? i : n - 1;
+        return DJ{pos[3 * p], pos[3 * p + 1], pos[3 * p + 2], i < n ? mass[i] : 0.0};
     };
     DJ xi[K];
     Sum4 ai[K];
@@ -317,25 +320,32 @@ __attribute__((amdgpu_waves_per_eu(MODE == P3T_DIRECT_NEWTON ? 3 : 2))) void k_d
                 }
             }
         } else {
-            for (int s = 0; s < kWave; ++s) {
-                const double2 a = xy[s], b = zm[s];
-                if (MODE == P3T_DIRECT_HARD && !any_near<K>(xi, a.x, a.y, b.x, dc)) continue;
+            const int64_t left = n - ((int64_t)y * B + c * kWave);
+            auto own = [&](auto part) {
+                constexpr bool PART = decltype(part)::value;   // padding among the 64
+                for (int s = 0; s < kWave; ++s) {
+                    if (PART && ((lane + s) & (kWave - 1)) >= left) continue;
+                    const double2 a = xy[s], b = zm[s];
+                    if (MODE == P3T_DIRECT_HARD && !any_near<K>(xi, a.x, a.y, b.x, dc)) continue;
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    // a particle meets itself in step 0 of its own 64
-                    if (s == 0 && w * K + k == c) continue;
-                    const double dx = a.x - xi[k].x, dy = a.y - xi[k].y, dz = b.x - xi[k].z;
-                    const double r2 = __builtin_fma(
-                        dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, dc.eps2)));
-                    double f, ph;
-                    if (!pair_factors<MODE>(r2, dc, f, ph)) continue;
-                    const double fi = b.y * f;
-                    ai[k].x = __builtin_fma(fi, dx, ai[k].x);
-                    ai[k].y = __builtin_fma(fi, dy, ai[k].y);
-                    ai[k].z = __builtin_fma(fi, dz, ai[k].z);
-                    ai[k].p = __builtin_fma(-b.y, ph, ai[k].p);
+                    for (int k = 0; k < K; ++k) {
+                        // a particle meets itself in step 0 of its own 64
+                        if (s == 0 && w * K + k == c) continue;
+                        const double dx = a.x - xi[k].x, dy = a.y - xi[k].y, dz = b.x - xi[k].z;
+                        const double r2 = __builtin_fma(
+                            dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, dc.eps2)));
+                        double f, ph;
+                        if (!pair_factors<MODE>(r2, dc, f, ph)) continue;
+                        const double fi = b.y * f;
+                        ai[k].x = __builtin_fma(fi, dx, ai[k].x);
+                        ai[k].y = __builtin_fma(fi, dy, ai[k].y);
+                        ai[k].z = __builtin_fma(fi, dz, ai[k].z);
+                        ai[k].p = __builtin_fma(-b.y, ph, ai[k].p);
+                    }
                 }
-            }
+            };
+            if (left < kWave) own(std::true_type());
+            else own(std::false_type());
         }
     }
 #pragma unroll
