@@ -531,8 +531,8 @@ __global__ __launch_bounds__(kVjpThreads, sizeof(R) == 4 && !CELL_K ? 4 : 2) voi
         // particles: a lane per entry, the members from LDS; each pair's term
         // counts for both sides, the members' parts gathered as for the cells
         // below.  Far ones have K = W = 1 and are never a member; a near one may
-        // be, and adds nothing to itself.  Lanes past the end hold a massless
-        // particle far away, whose terms are exactly zero.
+        // be, and adds nothing to itself.  Lanes past the end add nothing (far ones
+        // hold a massless particle far away, whose terms are exactly zero).
         auto particles = [&](auto near, const int32_t *__restrict__ idx, int64_t count) {
             constexpr bool NEAR = decltype(near)::value;
             for (int64_t e0 = (int64_t)w * kWave; e0 < count; e0 += kVjpThreads) {
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(kVjpThreads, sizeof(R) == 4 && !CELL_K ? 4 : 2) voi
                         row_runs(r0, k1, lane, mg, [&](int k, R gd[3]) {
                             const VjpMember<R> q = s_i[k];
                             R gmj = R(0);
-                            if (NEAR && valid && s_id[k] == j)
+                            if (NEAR && (!valid || s_id[k] == j))
                                 gd[0] = gd[1] = gd[2] = R(0);
                             else
                                 pair_grad<R, NEAR>(xj - q.x, yj - q.y, zj - q.z, mj, q.wx, q.wy,

@@ -46,3 +46,23 @@ def test_vjp_alone(ctx, precision):  # noqa: F811
     gp, gm = _gpu_vjp(ctx, np.array([[0.3, -0.2, 0.1]]), np.array([1.0]), p, np.ones((1, 3)),
                       np.ones(1))
     assert np.all(gp == 0.0) and np.all(gm == 0.0)
+
+
+@pytest.mark.parametrize("n", [1, 17, 70])
+def test_vjp_near_far_out(ctx, n):  # noqa: F811
+    """Near lists (FP64) of a cluster whose coordinates are of the size of 1e18, without
+    softening, one particle at a round place: lanes past a list's end take no part."""
+    c = plummer(max(n, 2), 63)
+    pos = c.pos[:n] * 1e17 + 1e18
+    pos[0] = 1e18
+    mass = np.full(n, 1.0 / n)
+    p = dict(eps=0.0, r_in=1e16, r_out=1e17, theta=0.5, r_search=1.1e17, n_crit=80, n_leaf=16,
+             use_quadrupole=1, precision="fp64")
+    rng = np.random.default_rng(64)
+    w, cw = rng.normal(size=(n, 3)), rng.normal(size=n)
+    log(f"near vjp far out n={n}")
+    gp, gm = _gpu_vjp(ctx, pos, mass, p, w, cw)
+    op, om = oracle.Tree(pos, mass, p).vjp(w, cw)
+    assert np.all(np.isfinite(gp)) and np.all(np.isfinite(gm))
+    if n > 1:
+        _check_vjp(gp, gm, op, om, "fp64", "far out")
