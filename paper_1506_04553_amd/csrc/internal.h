@@ -31,7 +31,8 @@ struct alignas(32) PosMass {
 // Per-node record read by the tree walk (96 bytes, one read per visit).
 struct NodeWalk {
     double cx, cy, cz;      // centre of mass
-    double l2;              // squared cell side (L 2^-level)^2
+    double l2;              // squared cell side (L 2^-level)^2, negative where the centre of
+                            // mass lies outside the member box (com_in_box)
     double lo[3], hi[3];    // tight member box
     int32_t child_first, n_child, first, count;
 };

@@ -1029,6 +1029,14 @@ __device__ __forceinline__ void flush_tile_counts(const MomentArrays &A, const T
     }
 }
 
+// Whether the centre of mass c lies within the members' extent [lo, hi] of an axis, up
+// to a small part of the cell's side: not so where the masses or their products with
+// the positions leave the range of normal numbers.  The walk relies on it (walk_far2).
+__device__ __forceinline__ bool com_in_box(double c, double lo, double hi, double side) {
+    const double slack = 1e-4 * side;
+    return lo - c <= slack && c - hi <= slack;
+}
+
 // L: the root cell's side
 __device__ __forceinline__ void store_node(const MomentArrays &A, double L, int64_t id, int lev,
                                            int nc, int32_t child_first, int32_t f, int32_t cnt,
@@ -1042,7 +1050,9 @@ __device__ __forceinline__ void store_node(const MomentArrays &A, double L, int6
     const double side = ldexp(L, -lev);
     NodeWalk o;
     o.cx = cx; o.cy = cy; o.cz = cz;
-    o.l2 = side * side;
+    const bool in = com_in_box(cx, lo[0], hi[0], side) && com_in_box(cy, lo[1], hi[1], side) &&
+                    com_in_box(cz, lo[2], hi[2], side);
+    o.l2 = in ? side * side : -(side * side);
     for (int a = 0; a < 3; ++a) { o.lo[a] = lo[a]; o.hi[a] = hi[a]; }
     o.child_first = nc ? child_first : -1;
     o.n_child = nc;
@@ -1254,8 +1264,12 @@ __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, 
             const double next = q + qs[j];
             q = j < nc ? next : q;
         }
-        if (!mine) continue;
+        // (lanes 4 - 6 hold the extent of an axis)
         const double side = ldexp(L, -lev);
+        const uint64_t out =
+            ballot(c >= 4 && c < 7 && !com_in_box(c == 4 ? cx : c == 5 ? cy : cz, acc, hi, side));
+        if (!mine) continue;
+        const double l2 = out >> row & 0xff ? -(side * side) : side * side;
         const int32_t f = st.first[at];   // the node's first particle is its first child's
         const int32_t child_first = (int32_t)(k0 + at);
         auto pair = [](int32_t lo, int32_t hi) {
@@ -1265,7 +1279,7 @@ __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, 
         if (c >= 1 && c < 4) A.S[(c - 1) * A.n_nodes + id] = acc;
         double *const nw = reinterpret_cast<double *>(A.nw + id);
         double *const mp = reinterpret_cast<double *>(A.mp + id);
-        nw[c < 7 ? c : 10] = c < 3 ? com : c == 3 ? side * side : c < 7 ? acc : pair(child_first, nc);
+        nw[c < 7 ? c : 10] = c < 3 ? com : c == 3 ? l2 : c < 7 ? acc : pair(child_first, nc);
         if (c >= 4) nw[c < 7 ? c + 3 : 11] = c < 7 ? hi : pair(f, cnt);
         if (c < 4) mp[c] = c < 3 ? com : M;
         if (c < 6) mp[4 + c] = q;

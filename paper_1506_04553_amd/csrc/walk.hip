@@ -108,8 +108,8 @@ __device__ __forceinline__ bool walk_group(const GroupInfo &gi, const NodeWalk *
             const double t1 = gap(gi.lo[1] - nd.cy, nd.cy - gi.hi[1]);
             const double t2 = gap(gi.lo[2] - nd.cz, nd.cz - gi.hi[2]);
             const double D2 = t0 * t0 + t1 * t1 + t2 * t2;
-            acc = wp.th2 * D2 > l2;
-            if (!(LAZY && acc && D2 * wp.far2 >= wp.h2)) {
+            acc = wp.th2 * D2 > fabs(l2);
+            if (!(LAZY && acc && l2 > 0.0 && D2 * wp.far2 >= wp.h2)) {
                 const double b0 = gap(nd.lo[0] - gi.hi[0], gi.lo[0] - nd.hi[0]);
                 const double b1 = gap(nd.lo[1] - gi.hi[1], gi.lo[1] - nd.hi[1]);
                 const double b2 = gap(nd.lo[2] - gi.hi[2], gi.lo[2] - nd.hi[2]);
@@ -372,9 +372,10 @@ __global__ __launch_bounds__(1024) void k_walk_stats(const GroupInfo *__restrict
         host[k] = __hip_atomic_load(&from[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A cell's box and centre of mass lie in a cube of side l: its box is at most
-// sqrt(3) l nearer to a group than its centre.  So a cell with theta D > l has a
-// gap of at least D (1 - sqrt(3) theta), and where that exceeds h by more than
+// A cell's members lie in a cube of side l, and where its l2 says so their centre of
+// mass in the members' box, up to 1e-4 l: then the box is at most sqrt(3) (l + 1e-4 l)
+// nearer to a group than the centre.  So a cell with theta D > l has a gap of at
+// least D (1 - sqrt(3) theta), less 2e-4 D, and where that exceeds h by more than
 // any rounding, the test of the gap passes without the box.
 static double walk_far2(double theta) {
     const double c = 1.0 - 1.7321 * theta - 1e-3;
