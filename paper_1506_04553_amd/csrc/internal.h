@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "p3t.h"
+#include "sort_choice.h"
 
 namespace p3t {
 
@@ -111,7 +112,7 @@ struct p3t_ctx {
     int64_t *hpin = nullptr;      // pinned host readback area (kReadbackWords int64)
     void *scratch = nullptr;      // device address of the library's static workspace on this device
 
-    int64_t whole_sort_n = -1;    // particles of the builds that sort whole keys (tree.hip)
+    p3t::SortChoice sort_choice;  // of the radix sort (tree.hip)
     p3t::DevBuf root, keys[2], vals[2], hist, histc, rs_tot, xm, xm_in;
     p3t::DevBuf lvlrange, tblk, tblk_off, gtile;
     p3t::DevBuf node_level, node_first, node_count, node_child, node_nchild, node_parent,
@@ -183,6 +184,7 @@ static_assert(kRbWalk + kRbWalkWords <= kReadbackWords, "readback layout");
 // Tree build stages (tree.hip).
 // root cube, Morton keys, stable sort (keys[0] / vals[0]) and the sorted
 // particle records xm
+bool sorts_by_radix(int64_t n);
 int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n, bool whole);
 // sets ctx->n_nodes, level_start, depth; or *unsorted, where the keys still have to
 // be sorted whole

@@ -257,12 +257,12 @@ extern "C" int p3t_build_tree(p3t_ctx *ctx, int64_t n, const double *pos, const 
     ctx->chg = make_changeover(p->r_in, p->r_out);
     if ((rc = ensure_readback(ctx))) return rc;
     if ((rc = mark(ctx, EV_BUILD))) return rc;
-    // (where the short sort didn't do, the next builds of as many particles don't try)
+    const bool radix = sorts_by_radix(n), whole = radix && ctx->sort_choice.whole();
     bool unsorted = false;
-    if ((rc = build_sorted(ctx, pos, mass, n, ctx->whole_sort_n == n))) return rc;
+    if ((rc = build_sorted(ctx, pos, mass, n, whole))) return rc;
     if ((rc = build_topology(ctx, n, &unsorted))) return rc;
+    if (radix && !whole) ctx->sort_choice.tried(unsorted);
     if (unsorted) {
-        ctx->whole_sort_n = n;
         if ((rc = build_sorted(ctx, pos, mass, n, true))) return rc;
         if ((rc = build_topology(ctx, n, &unsorted))) return rc;
     }

@@ -600,6 +600,8 @@ static bool group_tiles_counted(const p3t_ctx *ctx, int64_t n) {
     return !ctx->groups_generic && (n + 1 + kScan2Tile - 1) / kScan2Tile <= kScan2MaxTiles;
 }
 
+bool sorts_by_radix(int64_t n) { return n > kRankKeysMax; }
+
 // Root cube, keys, the radix passes, and the sorted particle records: the first
 // digit's histogram comes with the keys, the records with the last pass.  `whole`:
 // pass over all bits of the keys.
