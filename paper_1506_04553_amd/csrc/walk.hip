@@ -237,7 +237,7 @@ struct WalkStats {
     unsigned long long blocks_done, pad;   // blocks of the statistics kernel
     // per launch-order bucket (see below): groups, their cost, and what their
     // partial sums would take if they were split (FP32: exactly; FP64: members
-    // times cost)
+    // times cost over rounds, which the share of a part still divides)
     unsigned long long bin[kOrderBins], bin_cost[kOrderBins], bin_room[kOrderBins];
     unsigned long long bin_rounds[kOrderBins];   // rounds of the interaction kernel
 };
@@ -312,9 +312,11 @@ __global__ __launch_bounds__(1024) void k_walk_stats(const GroupInfo *__restrict
             const float cost = group_cost(ng, c[0], c[1] + c[2]);
             const int b = cost_bin(cost);
             atomicAdd(&s_cost[b], (unsigned long long)cost);
-            atomicAdd(&s_room[b], wide ? n * (unsigned long long)cost
-                                       : (unsigned long long)fp32_room(ng, c[0], c[1], c[2]));
-            atomicAdd(&s_rounds[b], (unsigned long long)rounds_of(ng, wide));
+            const int rounds = rounds_of(ng, wide);
+            atomicAdd(&s_room[b],
+                      wide ? (unsigned long long)((float)ng * (cost + 1.0f) / (float)rounds) + 1
+                           : (unsigned long long)fp32_room(ng, c[0], c[1], c[2]));
+            atomicAdd(&s_rounds[b], (unsigned long long)rounds);
             const int32_t r = (b << 24) | (int32_t)atomicAdd(&s_bin[b], 1u);
             if (g == t0) first_rank = r; else rank[g] = r;
         }
@@ -415,13 +417,14 @@ ListsDev lists_dev(const p3t_ctx *ctx) {
     return L;
 }
 
-// What splits: the groups of the first buckets, into parts of about `share`.
+// What splits: the groups of the first buckets, into rounds, and those of the first
+// of these, whose partial sums have room, into parts of about `share`.
 struct SplitPlan {
     int last_bin;          // groups of buckets 0 .. last_bin are split (-1: none)
+    int last_cut;          // ... and of buckets 0 .. last_cut cut into parts
     int first_whole;       // work items kept for them
     bool wide;             // FP64
     float share;
-    int64_t room;          // partial sums there is room for
     int32_t *n_items;      // device counters, zero before the launch
     unsigned long long *used;
     SplitGroup *group;     // [G], written for the groups of the split buckets
@@ -432,7 +435,7 @@ constexpr int kMaxParts = 256;
 // Group order from the ranks, and the work items: each block takes the bucket
 // starts (exclusive scan of the counts) itself.  A group of the split buckets
 // becomes one item per round and part, with up to one part per unit of its
-// lists; if the partial sums' room is used up its lists stay whole.
+// lists.
 __global__ __launch_bounds__(256) void k_order_place(int64_t G, const int32_t *__restrict__ rank,
                                                      const unsigned long long *__restrict__ bins,
                                                      int32_t *__restrict__ order,
@@ -470,7 +473,7 @@ __global__ __launch_bounds__(256) void k_order_place(int64_t G, const int32_t *_
         const int64_t units = units_of(c, tiles) + units_of(f, tiles) + units_of(n, tiles);
         rounds = rounds_of(ng, sp.wide);
         const int64_t want = (int64_t)ceilf(group_cost(ng, c, f + n) / (sp.share * (float)rounds));
-        parts = (int)min<int64_t>(min<int64_t>(want, units), kMaxParts);
+        parts = bin > sp.last_cut ? 1 : (int)min<int64_t>(min<int64_t>(want, units), kMaxParts);
         if (parts < 1) parts = 1;
         room = parts == 1 ? 0 : sp.wide ? (int64_t)parts * ng : fp32_room(ng, c, f, n);
     }
@@ -478,7 +481,6 @@ __global__ __launch_bounds__(256) void k_order_place(int64_t G, const int32_t *_
     int64_t rbase = 0;
     if (lane_id() == kWave - 1) rbase = (int64_t)atomicAdd(sp.used, (unsigned long long)rincl);
     rbase = __shfl(rbase, kWave - 1, kWave) + rincl - room;
-    if (rbase + room > sp.room) parts = split ? 1 : 0;
     const int incl = wave_incl_scan(parts * rounds);
     int32_t base = 0;
     if (lane_id() == kWave - 1) base = atomicAdd(sp.n_items, incl);
@@ -527,37 +529,43 @@ WorkDev work_dev(const p3t_ctx *ctx) {
 // a share split).
 constexpr int kBlocks64 = 256 * 4, kBlocks32 = 256 * 5;   // blocks in flight on 256 CUs
 constexpr int kFewGroups64 = 2 * kBlocks64;
-constexpr int64_t kSplitScratch = (int64_t)256 << 20;    // bound on the partial sums' bytes
+// Bound on the partial sums' bytes.  FP64 stays below it: a group in p > 1 parts, the
+// next whole number to c = cost / (share rounds), takes less than 2 c sums of a member,
+// and the members of a round are at most 512, so that all groups together take at most
+// 2 x 512 x 4 x 1024 of 32 bytes.  FP32 reaches it with the longest lists, and cuts the
+// costliest groups.
+constexpr int64_t kSplitScratch = (int64_t)256 << 20;
 static int plan_split(p3t_ctx *ctx, SplitPlan &sp) {
     int rc;
     const WalkStats *hs = walk_stats_host(ctx);
     const bool wide = ctx->prm.precision == P3T_PREC_FP64;
-    sp = SplitPlan{-1, 0, wide, 1.0f, 0, nullptr, nullptr, nullptr, nullptr};
+    sp = SplitPlan{-1, -1, 0, wide, 1.0f, nullptr, nullptr, nullptr, nullptr};
     const double cost = 35.0 * (double)hs->pc + 15.0 * (double)hs->pp;
     const double share =
         cost / (wide ? (ctx->n_groups <= kFewGroups64 ? 4.0 : 1.0) * kBlocks64 : 2.0 * kBlocks32) + 1.0;
     const int last = wide ? cost_bin((float)share)
                           : ctx->n_groups <= kBlocks32 ? kOrderBins - 1 : -1;
     int64_t groups = 0, rounds = 0;
-    double work = 0.0, room = 0.0;
+    double work = 0.0, sums = 0.0, room = 0.0;   // sums: FP32 partial sums, FP64 without rounding up
+    const size_t one = 4 * (wide ? sizeof(double) : sizeof(float));
     for (int b = 0; b <= last; ++b) {
         groups += (int64_t)hs->bin[b];
         work += (double)hs->bin_cost[b];
-        room += (double)hs->bin_room[b];
         rounds += (int64_t)hs->bin_rounds[b];
+        sums += (double)hs->bin_room[b] / (wide ? share : 1.0);
+        // (rounding parts up adds at most as many sums again, or one of each particle)
+        const double most = wide ? 1.0001 * (sums + fmin(sums, (double)ctx->n)) : sums;
+        if (most * (double)one > (double)kSplitScratch || sp.last_cut < b - 1) continue;
+        sp.last_cut = b;
+        room = most;
     }
     // each group: at most cost / share + rounds (and rounding of the sums)
     const int64_t items = groups ? (int64_t)(work / share * 1.0001) + groups + rounds : 0;
-    const size_t one = 4 * (wide ? sizeof(double) : sizeof(float));
-    // FP64: a group of n members and p <= cost / share + 1 parts takes n p sums
-    if (wide) room = room / share + (double)ctx->n;
-    if (room * (double)one > (double)kSplitScratch) room = (double)(kSplitScratch / one);
     if (groups) {
         sp.last_bin = last;
         sp.first_whole = (int)items;
         sp.share = (float)share;
-        sp.room = (int64_t)room;
-        if ((rc = ensure(ctx, ctx->fpart, (size_t)sp.room * one))) return rc;
+        if ((rc = ensure(ctx, ctx->fpart, ((size_t)room + 1) * one))) return rc;
         sp.n_items = &walk_stats_dev(ctx)->n_items;
         sp.used = &walk_stats_dev(ctx)->part_used;
     }
