@@ -171,7 +171,9 @@ int p3t_long_force_vjp_noalloc(p3t_ctx *ctx, const double *w, const double *c, d
                                double *gmass);
 
 /* Frees the interaction-list arrays of the last build (the largest part of a
- * build's memory) and keeps the tree, moments and groups.  The next call that
+ * build's memory), the partial sums of groups that several blocks share (up to 288
+ * MiB) and the workspace of the direct sums, and keeps the tree, moments and groups.
+ * The next call that
  * needs the lists (p3t_long_force, p3t_neighbors, p3t_long_force_vjp,
  * p3t_step, p3t_copy_array of a list) walks the tree again first; the walk is
  * deterministic, so the lists, forces and VJP are the same as without the
@@ -320,10 +322,11 @@ int p3t_step(p3t_ctx *ctx, int64_t n, double *pos, double *vel, const double *ma
  * (Section 2.1: F_soft and F_hard, H_soft and H_hard; d = x_j - x_i, s the
  * softened distance).  O(n^2) work; uses eps, r_in, r_out of *p.
  *   pos device [n][3]; mass device [n]; acc device [n][3] out; pot device [n]
- *   out or NULL.  The context keeps a workspace of 256 MiB (64 n bytes beyond four
- *   million particles) for it; without memory for that, and under stream capture,
- *   the call takes none and evaluates every pair from both sides.  Errors: EINVAL,
- *   EHIP. */
+ *   out or NULL.  The context keeps a workspace for it until p3t_release_lists or
+ *   p3t_destroy: up to 288 MiB, less for fewer than about 90000 particles (13 MiB for
+ *   5000), 72 n bytes beyond four million; without memory for that, and under stream
+ *   capture, the call takes none and evaluates every pair from both sides.  Errors:
+ *   EINVAL, EHIP. */
 #define P3T_DIRECT_NEWTON 0
 #define P3T_DIRECT_SOFT 1
 #define P3T_DIRECT_HARD 2

@@ -293,9 +293,10 @@ extern "C" int p3t_release_lists(p3t_ctx *ctx) {
     if (rc) return rc;
     // the stream's work may still read the lists: free only after it drains
     if ((rc = check_hip(ctx, hipStreamSynchronize(ctx->stream), "sync"))) return rc;
-    release(ctx, ctx->c_idx);
-    release(ctx, ctx->p_idx);
-    release(ctx, ctx->n_idx);
+    // (the partial sums are sized again with the next lists, the direct sums' rows by
+    // the next call that needs them)
+    for (DevBuf *b : {&ctx->c_idx, &ctx->p_idx, &ctx->n_idx, &ctx->fpart, &ctx->direct_rows})
+        release(ctx, *b);
     ctx->lists_released = 1;
     return P3T_OK;
 }
