@@ -587,7 +587,8 @@ static int build_order(p3t_ctx *ctx, int64_t stride) {
     if ((rc = ensure(ctx, ctx->gorder, (G + 1) * sizeof(int32_t)))) return rc;
     ctx->n_split = ctx->n_items = 0;
     if (G <= 0) return P3T_OK;
-    if (G >= (1 << 24)) {   // ranks are packed in 24 bits: keep the group order
+    // ranks are packed in 24 bits: beyond, keep the group order, every group whole
+    if (G >= (1 << 24) || ctx->groups_generic) {
         if ((rc = ensure(ctx, ctx->work, (size_t)G * sizeof(WorkItem)))) return rc;
         k_order_identity<<<blocks_for(G, 256), 256, 0, ctx->stream>>>(G, ptr<int32_t>(ctx->gorder),
                                                                      ptr<WorkItem>(ctx->work));
