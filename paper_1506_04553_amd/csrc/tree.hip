@@ -241,6 +241,7 @@ __device__ __forceinline__ uint64_t morton_key(const PosMass &r, const double lo
     return (spread_bits3(q[0]) << 2) | (spread_bits3(q[1]) << 1) | spread_bits3(q[2]);
 }
 
+// (counts: null where no radix pass follows)
 __global__ __launch_bounds__(kRsThreads) void k_keys_hist(const double *__restrict__ pos,
                                                           const double *__restrict__ mass, int64_t n,
                                                           const double *__restrict__ partial,
@@ -271,8 +272,9 @@ __global__ __launch_bounds__(kRsThreads) void k_keys_hist(const double *__restri
         keys[i] = key;
         idx[i] = (int32_t)i;
         xm_in[i] = r[k];
-        atomicAdd(&h[rs_digit(key, shift)], 1);
+        if (counts) atomicAdd(&h[rs_digit(key, shift)], 1);
     }
+    if (!counts) return;
     __syncthreads();
     for (int d = threadIdx.x; d < kRsBins; d += kRsThreads)
         counts[(int64_t)d * nb + blockIdx.x] = h[d];
@@ -630,9 +632,12 @@ int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n,
         if ((rc = ensure(ctx, *b, n * sizeof(uint64_t)))) return rc;
     for (p3t::DevBuf *b : {&ctx->vals[0], &ctx->vals[1]})
         if ((rc = ensure(ctx, *b, n * sizeof(int32_t)))) return rc;
-    if ((rc = ensure(ctx, ctx->hist, (size_t)kRsBins * nb * sizeof(int32_t)))) return rc;
-    if ((rc = ensure(ctx, ctx->histc, (size_t)kRsBins * nb * sizeof(int32_t)))) return rc;
-    if ((rc = ensure(ctx, ctx->rs_tot, kRsBins * sizeof(int32_t)))) return rc;
+    const bool radix = sorts_by_radix(n);
+    if (radix) {
+        if ((rc = ensure(ctx, ctx->hist, (size_t)kRsBins * nb * sizeof(int32_t)))) return rc;
+        if ((rc = ensure(ctx, ctx->histc, (size_t)kRsBins * nb * sizeof(int32_t)))) return rc;
+        if ((rc = ensure(ctx, ctx->rs_tot, kRsBins * sizeof(int32_t)))) return rc;
+    }
     if ((rc = ensure(ctx, ctx->xm_in, n * sizeof(PosMass)))) return rc;
     double *partial = ptr<double>(ctx->bbox);
     k_bbox<<<nbb, kRedThreads, 0, ctx->stream>>>(pos, mass, n, partial);
@@ -646,9 +651,10 @@ int build_sorted(p3t_ctx *ctx, const double *pos, const double *mass, int64_t n,
                                                      ctx->hpin + kRbTopoBad,
                                                      ptr<uint64_t>(ctx->keys[0]),
                                                      ptr<int32_t>(ctx->vals[0]),
-                                                     ptr<PosMass>(ctx->xm_in), shift0, cnt, nb);
+                                                     ptr<PosMass>(ctx->xm_in), shift0,
+                                                     radix ? cnt : nullptr, nb);
     if ((rc = check_hip(ctx, hipGetLastError(), "root/keys"))) return rc;
-    if (n <= kRankKeysMax) {
+    if (!radix) {
         k_rank_keys<<<blocks_for(n, kWave), kRankThreads, 0, ctx->stream>>>(
             ptr<uint64_t>(ctx->keys[0]), ptr<PosMass>(ctx->xm_in), (int)n,
             ptr<uint64_t>(ctx->keys[1]), ptr<int32_t>(ctx->vals[1]), ptr<PosMass>(ctx->xm),
@@ -917,7 +923,8 @@ int build_topology(p3t_ctx *ctx, int64_t n, bool *unsorted) {
     // n + 1: the array later holds the groups' node_at
     if ((rc = ensure(ctx, ctx->lvlrange, (n + 1) * sizeof(int32_t)))) return rc;
     if ((rc = ensure(ctx, ctx->tblk, (size_t)kLevels * nb * sizeof(int32_t)))) return rc;
-    if ((rc = ensure(ctx, ctx->tblk_off, (size_t)kLevels * nb * sizeof(int32_t)))) return rc;
+    const bool few = nb <= kTopoFew;
+    if (!few && (rc = ensure(ctx, ctx->tblk_off, (size_t)kLevels * nb * sizeof(int32_t)))) return rc;
     if ((rc = ensure_readback(ctx))) return rc;
     const uint64_t *keys = ptr<uint64_t>(ctx->keys[0]);
     int32_t *blk = ptr<int32_t>(ctx->tblk), *blk_off = ptr<int32_t>(ctx->tblk_off);
@@ -925,7 +932,6 @@ int build_topology(p3t_ctx *ctx, int64_t n, bool *unsorted) {
     const int64_t n_gtile = (n + 1 + kScan2Tile - 1) / kScan2Tile;
     const bool gcount = group_tiles_counted(ctx, n);
     if (gcount && (rc = ensure(ctx, ctx->gtile, n_gtile * sizeof(int32_t)))) return rc;
-    const bool few = nb <= kTopoFew;
     int32_t *starts = reinterpret_cast<int32_t *>(ctx->hpin + kRbWalk);   // (few)
     k_topo_ranges<<<nb, kTopoThreads, 0, ctx->stream>>>(
         keys, n, ctx->prm.n_leaf, ptr<int32_t>(ctx->lvlrange), blk, nb,
@@ -1433,14 +1439,11 @@ __global__ __launch_bounds__(kScan2Threads) void k_group_tiles(const int32_t *__
     if (tid == 0 && blockIdx.x == gridDim.x - 1) *slot_n = start + total;
 }
 
-// (more than kScan2MaxTiles tiles of particles) also clears the walk's
-// statistics words (zero, nz of them)
+// (more than kScan2MaxTiles tiles of particles)
 __global__ void k_group_compact(int64_t n, const int32_t *__restrict__ flag,
                                 const int32_t *__restrict__ slot, const int32_t *__restrict__ node_at,
-                                const NodeWalk *__restrict__ nw, GroupInfo *__restrict__ grp,
-                                int64_t *__restrict__ zero, int nz) {
+                                const NodeWalk *__restrict__ nw, GroupInfo *__restrict__ grp) {
     int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (a < nz) zero[a] = 0;
     if (a >= n || !flag[a]) return;
     const int32_t id = node_at[a];
     grp[slot[a]] = group_info(nw[id], id);
@@ -1467,9 +1470,8 @@ int build_groups(p3t_ctx *ctx) {
         return check_hip(ctx, hipGetLastError(), "groups");
     }
     if ((rc = scan_exclusive_i32(ctx, flag, slot, n + 1, nullptr))) return rc;
-    k_group_compact<<<blocks_for(n > kRbWalkWords ? n : kRbWalkWords, 256), 256, 0, ctx->stream>>>(
-        n, flag, slot, node_at, ptr<NodeWalk>(ctx->node_walk), ptr<GroupInfo>(ctx->grp),
-        ptr<int64_t>(ctx->readback) + kRbWalk, kRbWalkWords);
+    k_group_compact<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(
+        n, flag, slot, node_at, ptr<NodeWalk>(ctx->node_walk), ptr<GroupInfo>(ctx->grp));
     return check_hip(ctx, hipGetLastError(), "group compact");
 }
 
