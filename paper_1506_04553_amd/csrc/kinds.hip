@@ -91,19 +91,25 @@ __host__ __device__ inline int64_t normal_blocks(int64_t first_sp) {
     return (first_sp + kKindThreads - 1) / kKindThreads;
 }
 
-// normal particles: add the pulls of the special particles; special particles:
-// the pulls of every other particle, summed over the block
+// normal particles: add the pulls of the special particles (SHARE threads to a
+// particle); special particles: the pulls of every other particle, summed over the
+// block
+template <int SHARE>
 __global__ __launch_bounds__(kKindThreads) void k_kinds_soft(
     const double *__restrict__ pos, const double *__restrict__ mass, KindsConsts kc,
     double *__restrict__ acc, double *__restrict__ pot) {
     __shared__ double s_r[kKindWaves][4];
-    const int64_t nb = normal_blocks(kc.first_sp);
+    const int64_t nb = normal_blocks(SHARE * kc.first_sp);
     double r[4] = {0.0, 0.0, 0.0, 0.0};          // a and phi
     if (blockIdx.x < nb) {
-        const int64_t i = (int64_t)blockIdx.x * kKindThreads + threadIdx.x;
+        const int64_t i = ((int64_t)blockIdx.x * kKindThreads + threadIdx.x) / SHARE;
         if (i >= kc.first_sp) return;
-        for (int64_t b = kc.first_sp; b < kc.n; ++b)
+        const int part = threadIdx.x % SHARE;
+        for (int64_t b = kc.first_sp + part; b < kc.n; b += SHARE)
             soft_pull(pos + 3 * i, pos + 3 * b, mass[b], kc.ns, r, r[3]);
+        for (int d = 1; d < SHARE; d <<= 1)
+            for (int q = 0; q < 4; ++q) r[q] += __shfl_xor(r[q], d, kWave);
+        if (part != 0) return;
         for (int q = 0; q < 3; ++q) acc[3 * i + q] += r[q];
         if (pot) pot[i] += r[3];
         return;
@@ -230,8 +236,16 @@ int launch_kinds_soft(p3t_ctx *ctx, int64_t n, const double *pos, const double *
     (void)p;
     if (!kd || kd->n_special == 0) return P3T_OK;
     const KindsConsts kc = kinds_consts(n, kd);
-    k_kinds_soft<<<(unsigned)(normal_blocks(kc.first_sp) + kd->n_special), kKindThreads, 0,
-                   ctx->stream>>>(pos, mass, kc, acc, pot);
+    // A normal particle's sum is a chain as long as the special particles are many, a
+    // special one's as long as the normal blocks are: several threads to a normal
+    // particle where its chain is the longer (us with 1, 4 and 16: 6000 particles, 64 of
+    // them special, 43, 15 and 10; 30000, 128: 83, 31 and 41; 60000, 64: 53, 62 and 64;
+    // 300000, 512: 973, 842 and 828).
+    const int64_t blocks = normal_blocks(kc.first_sp);
+    const int share = kd->n_special <= blocks + blocks / 4 ? 1 : kd->n_special <= 8 * blocks ? 4 : 16;
+    auto kernel = share == 16 ? k_kinds_soft<16> : share == 4 ? k_kinds_soft<4> : k_kinds_soft<1>;
+    kernel<<<(unsigned)(normal_blocks(share * kc.first_sp) + kd->n_special), kKindThreads, 0,
+             ctx->stream>>>(pos, mass, kc, acc, pot);
     return check_hip(ctx, hipGetLastError(), "kinds soft");
 }
 
