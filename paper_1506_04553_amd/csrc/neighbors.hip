@@ -182,6 +182,14 @@ __global__ void k_sort_rows(int64_t n, const int64_t *__restrict__ off, int64_t 
 // readback slots (int64 units) used here: neighbour total, overflow flag, longest row
 enum { RB_NNZ = 40, RB_NOVF = 41, RB_NMAX = 42 };
 
+// the row lengths and slots are read up to this point of the context's stream: the
+// next search, which writes them on its own stream, waits for it
+static int rows_done(p3t_ctx *ctx) {
+    const int rc = check_hip(ctx, hipEventRecord(ctx->ev_sync[2], ctx->stream), "event record");
+    if (rc == P3T_OK) ctx->rows_packed = true;
+    return rc;
+}
+
 // The search, the scan of the row lengths and their readback run on a second
 // stream (the hard part's first auxiliary stream, idle outside its calls) as
 // soon as the walk's lists are complete, beside the interaction kernel or
@@ -218,6 +226,10 @@ int launch_neighbors(p3t_ctx *ctx, int64_t *offsets, int32_t *idx, int64_t cap, 
     const unsigned long long tag = ++ctx->nbr_tag;
     auto *rbu = reinterpret_cast<unsigned long long *>(rb);
     if ((rc = check_hip(ctx, hipStreamWaitEvent(as, ctx->ev_lists, 0), "wait"))) return rc;
+    // the last call's rows may still be on their way out of the workspaces
+    if (ctx->rows_packed &&
+        (rc = check_hip(ctx, hipStreamWaitEvent(as, ctx->ev_sync[2], 0), "wait")))
+        return rc;
     if (fresh) {
         if ((rc = check_hip(ctx, hipEventRecord(ctx->ev_sync[0], st), "event record"))) return rc;
         if ((rc = check_hip(ctx, hipStreamWaitEvent(as, ctx->ev_sync[0], 0), "wait"))) return rc;
@@ -255,7 +267,8 @@ int launch_neighbors(p3t_ctx *ctx, int64_t *offsets, int32_t *idx, int64_t cap, 
     if (!over) {
         k_pack_rows<<<blocks_for(n + 1, 256), 256, 0, st>>>(n, row_cap, ptr<int32_t>(ctx->nbr_slots),
                                                             cnt, offsets, idx);
-        return check_hip(ctx, hipGetLastError(), "neighbour pack");
+        if ((rc = check_hip(ctx, hipGetLastError(), "neighbour pack"))) return rc;
+        return rows_done(ctx);
     }
     // some row did not fit its slot: write the rows straight into the CSR
     if (grid) {
@@ -265,7 +278,8 @@ int launch_neighbors(p3t_ctx *ctx, int64_t *offsets, int32_t *idx, int64_t cap, 
         if ((rc = check_hip(ctx, hipGetLastError(), "neighbours (CSR)"))) return rc;
     }
     k_sort_rows<<<blocks_for(n + 1, 256), 256, 0, st>>>(n, cnt, offsets, idx);
-    return check_hip(ctx, hipGetLastError(), "neighbour sort");
+    if ((rc = check_hip(ctx, hipGetLastError(), "neighbour sort"))) return rc;
+    return rows_done(ctx);
 }
 
 }  // namespace p3t
