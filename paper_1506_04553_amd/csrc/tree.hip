@@ -1165,6 +1165,35 @@ __global__ __launch_bounds__(128) void k_moments_leaves(MomentArrays A, int32_t 
     }
 }
 
+// A parent whose only child is staged at `at`, on one thread, by the operations of
+// the fold below.
+__device__ __forceinline__ void fold_single(const MomentArrays &A, const MomStage &st, double L,
+                                            int lev, int32_t id, int32_t child, int at,
+                                            TileCount &tc) {
+    const double M = 0.0 + st.d[kChM][at], Sx = 0.0 + st.d[kChS][at],
+                 Sy = 0.0 + st.d[kChS + 1][at], Sz = 0.0 + st.d[kChS + 2][at];
+    const double dx = st.d[kChCom][at] - Sx / M, dy = st.d[kChCom + 1][at] - Sy / M,
+                 dz = st.d[kChCom + 2][at] - Sz / M;
+    const double r2 = dx * dx + dy * dy + dz * dz;
+    const double on[6] = {M * (3.0 * dx * dx - r2), M * (3.0 * dy * dy - r2),
+                          M * (3.0 * dz * dz - r2), M * 3.0 * dx * dy,
+                          M * 3.0 * dx * dz,        M * 3.0 * dy * dz};
+    double lo[3], hi[3], q[6];
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = st.d[kChLo + a][at];
+        hi[a] = st.d[kChHi + a][at];
+    }
+    for (int a = 0; a < 6; ++a) q[a] = 0.0 + (st.d[kChQ + a][at] + on[a]);
+    const int32_t cnt = st.count[at], f = st.first[at];
+    store_node(A, L, id, lev, 1, child, f, cnt, M, Sx, Sy, Sz, lo, hi, q);
+    A.count[id] = cnt;
+    if (cnt > A.n_crit) {
+        if (st.n_child[at] == 0) mark_group(A, child, f, tc);
+    } else if (lev == 0) {
+        mark_group(A, id, f, tc);
+    }
+}
+
 // The internal nodes of level lev whose first child lies in the chunk of
 // children [k0, k0 + kMomChunk) of the children level [cb, ce).  A thread per
 // child stages that child's record in LDS, with the kMomChildMax children past
@@ -1208,27 +1237,47 @@ __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, 
     if (lane == 0 && w < kMomFlagWaves) st.starts[w] = flags;
     if (t == 0) st.starts[kMomFlagWaves] = ~0ull;
     __syncthreads();
-    int np = 0, rank = 0;
+    // the chunk's parents, and those of more than one child: how many, and how many
+    // of them before this wavefront
+    int np = 0, nm = 0, rank = 0, mrank = 0;
+    uint64_t many = 0;
     for (int v = 0; v < kMomChunk / kWave; ++v) {
         uint64_t f = st.starts[v];
+        const uint64_t next = f >> 1 | st.starts[v + 1] << (kWave - 1);
         // starts past the level's end are not parents
         const int64_t left = ce - (k0 + v * kWave);
         f &= left >= kWave ? ~0ull : left > 0 ? (1ull << left) - 1 : 0ull;
-        if (v < w) rank += __popcll(f);
+        if (v < w) {
+            rank += __popcll(f);
+            mrank += __popcll(f & ~next);
+        }
+        if (v == w) many = f & ~next;
         np += __popcll(f);
+        nm += __popcll(f & ~next);
     }
+    // Where parents of a single child (chains, as of coincident particles) make two
+    // passes of the loop below or more, their child's thread folds them: 20000
+    // particles in 400 places, 19 such levels, are built in 301 us, 402 otherwise.
+    constexpr int kPass = kMomThreads / kMomLanes;
+    const bool singles = (np + kPass - 1) / kPass - (nm + kPass - 1) / kPass >= 2;
+    TileCount tc;
     if (t < kMomChunk && valid && start) {
-        rank += count_below(flags);
         const uint64_t next = lane == kWave - 1 ? st.starts[w + 1]
                                                 : (flags >> (lane + 1)) | (st.starts[w + 1] << (kWave - 1 - lane));
-        st.par[rank] = par;
-        st.at[rank] = t;
-        st.nc[rank] = __builtin_ctzll(next) + 1;
+        const int nc = __builtin_ctzll(next) + 1;
+        if (singles && nc == 1) {
+            fold_single(A, st, L, lev, par, (int32_t)k, t, tc);
+        } else {
+            rank = singles ? mrank + count_below(many) : rank + count_below(flags);
+            st.par[rank] = par;
+            st.at[rank] = t;
+            st.nc[rank] = nc;
+        }
     }
+    if (singles) np = nm;
     __syncthreads();
-    TileCount tc;
     const int c = t % kMomLanes, row = lane & ~(kMomLanes - 1);
-    for (int p0 = 0; p0 < np; p0 += kMomThreads / kMomLanes) {
+    for (int p0 = 0; p0 < np; p0 += kPass) {
         if (p0 + w * (kWave / kMomLanes) >= np) break;   // none for this wavefront
         const int p = p0 + t / kMomLanes;
         const bool mine = p < np;   // the same for a parent's lanes
