@@ -526,9 +526,15 @@ WorkDev work_dev(const p3t_ctx *ctx) {
 // groups', which costs more than it gains unless every group goes there, where
 // they are too few to fill the GPU (Plummer 1000: 86 us unsplit, 44 split;
 // Plummer 2^18, n_crit 128: 0.80 ms unsplit, 0.99 with the groups above half
-// a share split).
+// a share split).  Nor does it where there is a group for every compute unit and
+// none takes much longer than the others (20000 particles in 400 places, the largest
+// at most 1.7 times the mean: 36 us unsplit, 43 split, the VJP's two passes 96
+// and 108; 20000 on a line, 497 groups, 1.9: 117 and 136; but 20000 in a cube, 512
+// groups, 2.4: 71 and 60).
 constexpr int kBlocks64 = 256 * 4, kBlocks32 = 256 * 5;   // blocks in flight on 256 CUs
 constexpr int kFewGroups64 = 2 * kBlocks64;
+constexpr int kEvenGroups32 = 256;         // one for every CU
+constexpr double kEven32 = 2.0;            // the largest over the mean
 // Bound on the partial sums' bytes.  FP64 stays below it: a group in p > 1 parts, the
 // next whole number to c = cost / (share rounds), takes less than 2 c sums of a member,
 // and the members of a round are at most 512, so that all groups together take at most
@@ -543,8 +549,12 @@ static int plan_split(p3t_ctx *ctx, SplitPlan &sp) {
     const double cost = 35.0 * (double)hs->pc + 15.0 * (double)hs->pp;
     const double share =
         cost / (wide ? (ctx->n_groups <= kFewGroups64 ? 4.0 : 1.0) * kBlocks64 : 2.0 * kBlocks32) + 1.0;
+    int top = 0;   // the costliest groups' bucket: up to 2^((kOrderBins - top) / 4)
+    while (top < kOrderBins - 1 && !hs->bin[top]) ++top;
+    const bool even = ctx->n_groups >= kEvenGroups32 &&
+                      exp2((kOrderBins - top) / 4.0) * (double)ctx->n_groups < kEven32 * cost;
     const int last = wide ? cost_bin((float)share)
-                          : ctx->n_groups <= kBlocks32 ? kOrderBins - 1 : -1;
+                          : ctx->n_groups <= kBlocks32 && !even ? kOrderBins - 1 : -1;
     int64_t groups = 0, rounds = 0;
     double work = 0.0, sums = 0.0, room = 0.0;   // sums: FP32 partial sums, FP64 without rounding up
     const size_t one = 4 * (wide ? sizeof(double) : sizeof(float));
