@@ -136,10 +136,9 @@ struct p3t_ctx {
     int aux_ready = 0;
     // The neighbour search runs on aux[0] from the point where the lists are
     // complete (ev_lists, recorded on `stream` by every walk), beside whatever
-    // the context's stream does meanwhile; ev_sync orders the two: 0 fresh workspaces,
-    // 1 the search, 2 the packing of its rows (recorded where rows_packed).
-    hipEvent_t ev_lists = nullptr, ev_sync[3] = {nullptr, nullptr, nullptr};
-    bool rows_packed = false;
+    // the context's stream does meanwhile; ev_sync orders the two.
+    hipEvent_t ev_lists = nullptr, ev_sync[2] = {nullptr, nullptr};
+    bool rows_queued = false;   // rows of a search are packed after ev_lists
     p3t::DevBuf step_off, step_idx;    // neighbour CSR of p3t_step
     p3t::DevBuf step_off2, step_idx2;  // ... merged with the special particles' pairs
     p3t::DevBuf kinds_cnt;

@@ -182,14 +182,6 @@ __global__ void k_sort_rows(int64_t n, const int64_t *__restrict__ off, int64_t 
 // readback slots (int64 units) used here: neighbour total, overflow flag, longest row
 enum { RB_NNZ = 40, RB_NOVF = 41, RB_NMAX = 42 };
 
-// the row lengths and slots are read up to this point of the context's stream: the
-// next search, which writes them on its own stream, waits for it
-static int rows_done(p3t_ctx *ctx) {
-    const int rc = check_hip(ctx, hipEventRecord(ctx->ev_sync[2], ctx->stream), "event record");
-    if (rc == P3T_OK) ctx->rows_packed = true;
-    return rc;
-}
-
 // The search, the scan of the row lengths and their readback run on a second
 // stream (the hard part's first auxiliary stream, idle outside its calls) as
 // soon as the walk's lists are complete, beside the interaction kernel or
@@ -208,7 +200,8 @@ int launch_neighbors(p3t_ctx *ctx, int64_t *offsets, int32_t *idx, int64_t cap, 
     const int32_t row_cap = ctx->nbr_cap > 0 ? ctx->nbr_cap : kNbrFirstCap;
     // A workspace (re)allocated here may come from an allocator that hands out
     // memory which work still queued on the context's stream uses: the search
-    // then also waits for that work.
+    // then also waits for that work.  So does a search after another of the same
+    // lists, whose rows may still be on their way out of the workspaces.
     void *const had[3] = {ctx->nbr_cnt.p, ctx->nbr_slots.p, ctx->nbr_scan.p};
     if ((rc = ensure(ctx, ctx->nbr_cnt, (n + 1) * sizeof(int64_t)))) return rc;
     if ((rc = ensure(ctx, ctx->nbr_slots, (size_t)n * row_cap * sizeof(int32_t) + 4))) return rc;
@@ -226,11 +219,7 @@ int launch_neighbors(p3t_ctx *ctx, int64_t *offsets, int32_t *idx, int64_t cap, 
     const unsigned long long tag = ++ctx->nbr_tag;
     auto *rbu = reinterpret_cast<unsigned long long *>(rb);
     if ((rc = check_hip(ctx, hipStreamWaitEvent(as, ctx->ev_lists, 0), "wait"))) return rc;
-    // the last call's rows may still be on their way out of the workspaces
-    if (ctx->rows_packed &&
-        (rc = check_hip(ctx, hipStreamWaitEvent(as, ctx->ev_sync[2], 0), "wait")))
-        return rc;
-    if (fresh) {
+    if (fresh || ctx->rows_queued) {
         if ((rc = check_hip(ctx, hipEventRecord(ctx->ev_sync[0], st), "event record"))) return rc;
         if ((rc = check_hip(ctx, hipStreamWaitEvent(as, ctx->ev_sync[0], 0), "wait"))) return rc;
     }
@@ -267,8 +256,8 @@ int launch_neighbors(p3t_ctx *ctx, int64_t *offsets, int32_t *idx, int64_t cap, 
     if (!over) {
         k_pack_rows<<<blocks_for(n + 1, 256), 256, 0, st>>>(n, row_cap, ptr<int32_t>(ctx->nbr_slots),
                                                             cnt, offsets, idx);
-        if ((rc = check_hip(ctx, hipGetLastError(), "neighbour pack"))) return rc;
-        return rows_done(ctx);
+        ctx->rows_queued = true;
+        return check_hip(ctx, hipGetLastError(), "neighbour pack");
     }
     // some row did not fit its slot: write the rows straight into the CSR
     if (grid) {
@@ -278,8 +267,8 @@ int launch_neighbors(p3t_ctx *ctx, int64_t *offsets, int32_t *idx, int64_t cap, 
         if ((rc = check_hip(ctx, hipGetLastError(), "neighbours (CSR)"))) return rc;
     }
     k_sort_rows<<<blocks_for(n + 1, 256), 256, 0, st>>>(n, cnt, offsets, idx);
-    if ((rc = check_hip(ctx, hipGetLastError(), "neighbour sort"))) return rc;
-    return rows_done(ctx);
+    ctx->rows_queued = true;
+    return check_hip(ctx, hipGetLastError(), "neighbour sort");
 }
 
 }  // namespace p3t

@@ -183,7 +183,7 @@ extern "C" int p3t_create(p3t_ctx **out, int device, void *hip_stream, p3t_alloc
                                  hipHostMallocCoherent);
     for (int k = 0; k < 12 && e == hipSuccess; ++k) e = hipEventCreate(&ctx->ev[k]);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_lists, hipEventDisableTiming);
-    for (int k = 0; k < 3 && e == hipSuccess; ++k)
+    for (int k = 0; k < 2 && e == hipSuccess; ++k)
         e = hipEventCreateWithFlags(&ctx->ev_sync[k], hipEventDisableTiming);
     if (e != hipSuccess) {
         p3t_destroy(ctx);
@@ -221,7 +221,7 @@ extern "C" void p3t_destroy(p3t_ctx *ctx) {
     for (int k = 0; k < 5; ++k)
         if (ctx->aev[k]) (void)hipEventDestroy(ctx->aev[k]);
     if (ctx->ev_lists) (void)hipEventDestroy(ctx->ev_lists);
-    for (int k = 0; k < 3; ++k)
+    for (int k = 0; k < 2; ++k)
         if (ctx->ev_sync[k]) (void)hipEventDestroy(ctx->ev_sync[k]);
     delete ctx;
 }

@@ -628,6 +628,7 @@ static int run_walk_stats(p3t_ctx *ctx, const int32_t *G_dev, int64_t stride, Wa
 // context's stream: work on other streams that reads them waits for ev_lists
 static int lists_done(p3t_ctx *ctx, int rc) {
     if (rc) return rc;
+    ctx->rows_queued = false;
     return check_hip(ctx, hipEventRecord(ctx->ev_lists, ctx->stream), "event record");
 }
 
