@@ -418,10 +418,13 @@ static int launch_direct_mode(p3t_ctx *ctx, int64_t n, const double *pos, const 
                        cap == hipStreamCaptureStatusNone;
     if (plain) {
         // Blocks of 64 particles while blocks of 256 would leave most of the GPU
-        // idle (us, Newton / soft: 3000 particles 31 / 59 against 68 / 95, 6000
-        // 62 / 129 against 74 / 109), then of 256, then of 1024, whose rows
-        // are the shortest (32768 particles 621 / 792 against 510 / 600 with
-        // 256).
+        // idle (us, Newton / soft / hard: 4000 particles 39 / 68 / 34 against 71 / 90 /
+        // 46, 5000 54 / 109 / 44 against 73 / 91 / 49, 7000 75 / 169 / 60 against 78 /
+        // 102 / 53; one line between the three modes' own), then of 256, then of 1024,
+        // whose rows are the shortest (40000 particles 746 / 797 / 334 with 256
+        // against 873 / 1038 / 382, 49152 1114 / 1197 / 500 against 1104 / 1290 / 482,
+        // 80000 2812 / 3036 / 1232 against 2822 / 3175 / 1160; 2^18 take 9 launches
+        // instead of 33).
         const int rc = n <= 5000 ? direct_pairs<MODE, 1, 1>(ctx, n, pos, mass, dc, acc, pot)
                      : n <= 49152 ? direct_pairs<MODE, 4, 1>(ctx, n, pos, mass, dc, acc, pot)
                                   : direct_pairs<MODE, 4, 4>(ctx, n, pos, mass, dc, acc, pot);

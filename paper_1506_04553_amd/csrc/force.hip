@@ -7,7 +7,8 @@
 // with s the softened distance, y = s / r_out, K and W the changeover functions
 // of Section 2.1 (denominator of G read as (gamma - 1)^7).
 //
-// Kernel design (one block of four wavefronts per group):
+// Kernel design (one block of four wavefronts per work item: a group, or a part of a
+// split group's lists for one round of its members):
 //  * a lane is (i, slice): 64/s group members times s slices, each slice
 //    taking every s-th entry of a list tile; s (a power of two) is chosen per
 //    group to minimise padded lane work, so groups of any size keep the lanes
@@ -29,11 +30,14 @@
 //    middle branch is evaluated in FP64 in both paths (its monomial form
 //    cancels by two orders of magnitude).  Accepted cells lie at least h from
 //    the group, so their K = W = 1 is tested only when h < r_out;
-//  * a launch of one block per group ends with its largest group, so where
-//    groups are few they are split into parts of their lists (walk.hip decides
-//    which), a block each, whose sums k_force_fold adds up;
-//  * the mixed path accumulates each tile in FP32 and adds tile partials to a
-//    compensated (Kahan) FP32 sum per particle and component.
+//  * a launch of one block per group ends with its largest group, so where groups
+//    are few, and in FP64 where single ones stand out, they are split into rounds of
+//    their members and parts of their lists (plan_split in walk.hip says which), a
+//    block each; the parts' sums go to memory and k_force_fold adds them up in a
+//    fixed order.  FP32 has a kernel for whole groups and one, launched before it,
+//    for split ones; FP64 one kernel for both;
+//  * the mixed path accumulates tiles in FP32, at least 64 terms per lane, and adds
+//    these partials to a compensated (Kahan) FP32 sum per particle and component.
 #include <math.h>
 
 #include "device_util.h"

@@ -522,7 +522,9 @@ WorkDev work_dev(const p3t_ctx *ctx) {
 // 65536, Salpeter, 1734 groups: 0.90 ms unsplit, 0.56 at half a share, 0.51 at
 // a quarter; Plummer 4096: 155 and 29 us), a whole one where they are many and
 // only the largest stand out (King 500009, 6818 groups: 2.55 ms unsplit, 2.61
-// at a quarter).  FP32 has a launch of its own for the parts, before the whole
+// at a quarter).  The line is coarse: a whole share and a quarter take 178 and 165 us
+// at 1643 groups, 260 and 252 at 2671, 2118 and 2149 at 5517 of up to 256 members,
+// 1021 and 985 at 5620 of up to 128.  FP32 has a launch of its own for the parts, before the whole
 // groups', which costs more than it gains unless every group goes there, where
 // they are too few to fill the GPU (Plummer 1000: 86 us unsplit, 44 split;
 // Plummer 2^18, n_crit 128: 0.80 ms unsplit, 0.99 with the groups above half
