@@ -1238,29 +1238,40 @@ __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, 
     if (lane == 0 && w < kMomFlagWaves) st.starts[w] = flags;
     if (t == 0) st.starts[kMomFlagWaves] = ~0ull;
     __syncthreads();
-    // the chunk's parents, and those of more than one child: how many, and how many
-    // of them before this wavefront
-    int np = 0, nm = 0, rank = 0, mrank = 0;
-    uint64_t many = 0;
-    for (int v = 0; v < kMomChunk / kWave; ++v) {
-        uint64_t f = st.starts[v];
-        const uint64_t next = f >> 1 | st.starts[v + 1] << (kWave - 1);
-        // starts past the level's end are not parents
+    // the chunk's parents (starts past the level's end are not), and how many of them
+    // before this wavefront
+    auto starts_of = [&](int v) {
         const int64_t left = ce - (k0 + v * kWave);
-        f &= left >= kWave ? ~0ull : left > 0 ? (1ull << left) - 1 : 0ull;
-        if (v < w) {
-            rank += __popcll(f);
-            mrank += __popcll(f & ~next);
-        }
-        if (v == w) many = f & ~next;
-        np += __popcll(f);
-        nm += __popcll(f & ~next);
+        return st.starts[v] & (left >= kWave ? ~0ull : left > 0 ? (1ull << left) - 1 : 0ull);
+    };
+    int np = 0, rank = 0;
+    for (int v = 0; v < kMomChunk / kWave; ++v) {
+        const int c = __popcll(starts_of(v));
+        if (v < w) rank += c;
+        np += c;
     }
     // Where parents of a single child (chains, as of coincident particles) make two
     // passes of the loop below or more, their child's thread folds them: 20000
     // particles in 400 places, 19 such levels, are built in 301 us, 402 otherwise.
     constexpr int kPass = kMomThreads / kMomLanes;
-    const bool singles = (np + kPass - 1) / kPass - (nm + kPass - 1) / kPass >= 2;
+    bool singles = false;
+    if (np > 2 * kPass) {
+        int nm = 0, mrank = 0;       // the same for parents of more than one child
+        uint64_t many = 0;
+        for (int v = 0; v < kMomChunk / kWave; ++v) {
+            const uint64_t next = st.starts[v] >> 1 | st.starts[v + 1] << (kWave - 1);
+            const uint64_t f = starts_of(v) & ~next;
+            if (v < w) mrank += __popcll(f);
+            if (v == w) many = f;
+            nm += __popcll(f);
+        }
+        singles = (np + kPass - 1) / kPass - (nm + kPass - 1) / kPass >= 2;
+        if (singles) {
+            np = nm;
+            rank = mrank + count_below(many);
+        }
+    }
+    if (!singles) rank += count_below(flags);
     TileCount tc;
     if (t < kMomChunk && valid && start) {
         const uint64_t next = lane == kWave - 1 ? st.starts[w + 1]
@@ -1269,13 +1280,11 @@ __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, 
         if (singles && nc == 1) {
             fold_single(A, st, L, lev, par, (int32_t)k, t, tc);
         } else {
-            rank = singles ? mrank + count_below(many) : rank + count_below(flags);
             st.par[rank] = par;
             st.at[rank] = t;
             st.nc[rank] = nc;
         }
     }
-    if (singles) np = nm;
     __syncthreads();
     const int c = t % kMomLanes, row = lane & ~(kMomLanes - 1);
     for (int p0 = 0; p0 < np; p0 += kPass) {
@@ -1300,6 +1309,10 @@ __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, 
         const double M = __shfl(acc, row, kWave), Sx = __shfl(acc, row + 1, kWave),
                      Sy = __shfl(acc, row + 2, kWave), Sz = __shfl(acc, row + 3, kWave);
         const double cx = Sx / M, cy = Sy / M, cz = Sz / M;
+        // (lanes 4 - 6 hold the extent of an axis)
+        const double side = ldexp(L, -lev);
+        const uint64_t out =
+            ballot(c >= 4 && c < 7 && !com_in_box(c == 4 ? cx : c == 5 ? cy : cz, acc, hi, side));
         // the quadrupole (xx yy zz xy xz yz): each lane the six terms of one child,
         // each of six lanes then one component over the children
         double *const qt = st.q[t / kMomLanes];
@@ -1322,10 +1335,6 @@ __device__ __forceinline__ void fold_chunk(const MomentArrays &A, MomStage &st, 
             const double next = q + qs[j];
             q = j < nc ? next : q;
         }
-        // (lanes 4 - 6 hold the extent of an axis)
-        const double side = ldexp(L, -lev);
-        const uint64_t out =
-            ballot(c >= 4 && c < 7 && !com_in_box(c == 4 ? cx : c == 5 ? cy : cz, acc, hi, side));
         if (!mine) continue;
         const double l2 = out >> row & 0xff ? -(side * side) : side * side;
         const int32_t f = st.first[at];   // the node's first particle is its first child's
